@@ -216,7 +216,7 @@ def bench_overdecomposed(args):
     kernel_ms = sum(a.elapsed_time(b) for a, b in evs) / (args.steps * (sweeps - 1))
     glups = cells * sweeps / (ms_step * 1e-3) / 1e9
     achieved = per_launch / (kernel_ms * 1e-3) / 1e9
-    traffic_bytes = measured_traffic(args.edge, args.blocks) if args.mode == "graph" and not args.tune else None
+    traffic_bytes = measured_traffic(args.edge, args.blocks) if args.mode == "fused+graph" and not args.tune else None
     out = {
         "metric": METRIC, "value": round(glups, 3), "unit": "GLUP/s", "n_gpus": 1,
         "steps": args.steps, "warmup": args.warmup, "ms_per_step": round(ms_step, 3),
@@ -263,7 +263,7 @@ def side_configs(args, spec):
     log("[bench] config: modes of the overdecomposed grid")
     out["overdecomposed_modes"] = modes_side(spec)
     log("[bench] config: 1024^3 decompositions")
-    out["decompositions_1024"] = {"workload": "1024^3 FP64 grid, 500 sweeps (graph) per decomposition",
+    out["decompositions_1024"] = {"workload": "1024^3 FP64 grid, 500 sweeps (fused+graph) per decomposition",
                                   "runs": sweep_records(iters=args.sweep_iters)}
     from paper_2202_11819_amd import serve
     log("[bench] config: batched form")
@@ -293,14 +293,16 @@ def batch_bytes_per_lup():
 
 def modes_side(spec):
     """ms per sweep of the overdecomposed grid in the unfused modes (per block
-    and per phase), fused and graph; and whether the graph run equals the
-    undivided grid's bit for bit after the full sweep count."""
+    and per phase), fused, fused captured in graphs, and graph (several sweeps
+    per launch); and whether the graph run equals the undivided grid's bit for
+    bit after the full sweep count."""
     import torch
     from paper_2202_11819_amd import api
     n, sweeps = spec.n, spec.iters
     cells = n[0] * n[1] * n[2]
     res = {"workload": f"{n[0]}^3 as {spec.nblk[0]}x{spec.nblk[1]}x{spec.nblk[2]} blocks", "ms_per_sweep": {}}
-    for mode, iters in (("unfused_block", 6), ("unfused_phase", 100), ("fused", sweeps), ("graph", sweeps)):
+    for mode, iters in (("unfused_block", 6), ("unfused_phase", 100), ("fused", sweeps), ("fused+graph", sweeps),
+                        ("graph", sweeps)):
         with api.Solver(n, nblk=spec.nblk, seed=spec.seed) as s:
             s.run(2, mode=mode)
             torch.cuda.synchronize()
@@ -334,7 +336,8 @@ def bench_modes(args):
     cells = n[0] * n[1] * n[2]
     for mode, iters in [("unfused_block", 10), ("unfused_block+graph", 10), ("block_a", 10), ("block_b", 10),
                         ("block_c", 20), ("block_c+graph", 20), ("host_staged", 10), ("host_overlap", 10),
-                        ("unfused_phase", 100), ("fused", args.sweeps), ("graph", args.sweeps)]:
+                        ("unfused_phase", 100), ("fused", args.sweeps), ("fused+graph", args.sweeps),
+                        ("graph", args.sweeps)]:
         s2 = api.Solver(n, nblk=spec.nblk, seed=spec.seed)
         s2.run(2, mode=mode)
         torch.cuda.synchronize()
@@ -363,21 +366,25 @@ def sweep_records(iters=500):
         n = spec.n
         cells = n[0] * n[1] * n[2]
         s = api.Solver(n, nblk=spec.nblk, split=spec.split, seed=spec.seed)
-        s.run(10, mode="graph")
-        torch.cuda.synchronize()
-        e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-        e0.record(s.stream)
-        s.run(spec.iters, mode="graph")
-        e1.record(s.stream)
-        e1.synchronize()
-        ms = e0.elapsed_time(e1)
+        times = {}
+        for mode in ("graph", "fused+graph"):
+            s.run(10, mode=mode)
+            torch.cuda.synchronize()
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record(s.stream)
+            s.run(spec.iters, mode=mode)
+            e1.record(s.stream)
+            e1.synchronize()
+            times[mode] = e0.elapsed_time(e1)
+        ms = times["fused+graph"]
         per = sweep_bytes(s.problem)
         gbps = per * spec.iters / (ms * 1e-3) / 1e9
         nblocks = spec.nblk[0] * spec.nblk[1] * spec.nblk[2]
         recs.append({"workload": label, "blocks": nblocks, "value": round(cells * spec.iters / ms / 1e6, 3),
                      "unit": "GLUP/s", "GBps": round(gbps, 1), "hbm_frac": round(gbps / HBM_PEAK_GBPS, 4),
                      "B_per_LUP": round(per / cells, 3), "sweeps": spec.iters,
-                     "ms_per_sweep": round(ms / spec.iters, 4), "tune": list(s.get_tune()),
+                     "ms_per_sweep": round(ms / spec.iters, 4),
+                     "several_per_launch_GLUPs": round(cells * spec.iters / times["graph"] / 1e6, 3), "tune": list(s.get_tune()),
                      "tile": list(j3d.variants()[s.get_tune()[0]])})
         s.close()
         torch.cuda.empty_cache()
@@ -454,7 +461,7 @@ def bench_hostex(args):
 
 
 def bench_twostep(args):
-    """Two sweeps per launch against one, on the same grid left undivided (--edge, --sweeps)."""
+    """Several sweeps per launch against one, on the same grid left undivided (--edge, --sweeps)."""
     import torch
     from paper_2202_11819_amd import api
 
@@ -463,7 +470,7 @@ def bench_twostep(args):
     sweeps = args.sweeps - args.sweeps % 2
     with api.Solver(n, seed=1) as s:
         u0 = s.get_interior_device()
-        for mode in ("graph", "two_sweep"):
+        for mode in ("fused+graph", "two_sweep"):
             s.set_interior(u0)
             s.run(10, mode=mode)
             torch.cuda.synchronize()
@@ -473,17 +480,10 @@ def bench_twostep(args):
             e1.record()
             e1.synchronize()
             ms = e0.elapsed_time(e1)
-            per_launch = 2 if mode == "two_sweep" else 1
-            launches = sweeps // per_launch
-            # algorithmic bytes per launch: each cell read and written once, plus the boundary layer read
-            nbytes = 16 * cells + 16 * 3 * args.edge ** 2
-            gbps = nbytes * launches / (ms * 1e-3) / 1e9
-            print(json.dumps({"metric": "FP64 Jacobi3D GLUP/s, one vs two sweeps per launch", "grid": list(n),
+            print(json.dumps({"metric": "FP64 Jacobi3D GLUP/s, one vs several sweeps per launch", "grid": list(n),
                               "blocks": [1, 1, 1], "mode": mode, "sweeps": sweeps,
                               "value": round(cells * sweeps / ms / 1e6, 2), "unit": "GLUP/s",
-                              "ms_per_sweep": round(ms / sweeps, 4), "sweeps_per_launch": per_launch,
-                              "launch_ms": round(ms / launches, 4), "bytes_per_launch": nbytes,
-                              "GBps": round(gbps, 1), "hbm_frac": round(gbps / HBM_PEAK_GBPS, 4)}), flush=True)
+                              "ms_per_sweep": round(ms / sweeps, 4)}), flush=True)
         del u0
     torch.cuda.empty_cache()
 
@@ -495,7 +495,8 @@ def main():
     ap.add_argument("--warmup", type=int, default=1)
     ap.add_argument("--workload", default="overdecomposed",
                     choices=["overdecomposed", "modes", "sweep", "batch", "serve", "odf", "hostex", "twostep"])
-    ap.add_argument("--mode", default="graph", choices=["graph", "fused", "unfused_phase", "unfused_block"])
+    ap.add_argument("--mode", default="fused+graph",
+                    choices=["fused+graph", "graph", "fused", "unfused_phase", "unfused_block"])
     ap.add_argument("--edge", type=int, default=512)
     ap.add_argument("--blocks", type=int, default=8)
     ap.add_argument("--sweeps", type=int, default=1000)

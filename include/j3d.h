@@ -73,8 +73,13 @@ typedef enum {
  *                 straight from the neighbours' current iterate, updates, and
  *                 hands its new x faces to the neighbours' x-halo storage of
  *                 the next iterate; pack, exchange and unpack need no copy.
- *  GRAPH:         FUSED iterations captured once into a HIP graph holding an
- *                 even number of sweeps (both buffer parities), replayed.
+ *  GRAPH:         the fastest launches: several iterations each (temporal
+ *                 blocking, on decomposed grids too: a tile recomputes a ring
+ *                 of its neighbours' cells instead of exchanging halos between
+ *                 its iterations), captured into HIP graphs of an even number
+ *                 of launches, replayed.  After j3d_set_tune with a shape, and
+ *                 where the blocks lie too far apart or unequal ones are only a
+ *                 few planes deep, it is FUSED | CAPTURED.
  *  BLOCK_A/B/C:   the paper's fusion strategies at block granularity (one
  *                 launch stream of operations per block, like UNFUSED_BLOCK):
  *                 A fuses each block's six pack kernels into one; B also its
@@ -93,18 +98,15 @@ typedef enum {
  *                 block); once they are delivered and unpacked, the exterior
  *                 (the one-cell shell that reads halos) is updated.  Every
  *                 cell is written once per iteration.
- *  TWO_SWEEP:     two iterations per launch (temporal blocking) on a grid of
- *                 one block: each workgroup computes the intermediate iterate
- *                 on its tile plus a one-cell ring in LDS and writes only
- *                 every second iterate, halving the HBM traffic per
- *                 iteration.  An odd count ends with one FUSED sweep.  EINVAL
- *                 for a decomposed grid.  Not in the paper; it applies where
- *                 no block boundary needs an exchange.
+ *  TWO_SWEEP:     GRAPH's launches of several iterations each, not captured, on
+ *                 a grid of one block, whatever shape j3d_set_tune chose.
+ *                 EINVAL for a decomposed grid.  Not in the paper.
  *  CAPTURED:      a flag OR-ed with any mode: its iterations are captured once
- *                 into HIP graphs (50 sweeps per graph for FUSED, 48 for
- *                 TWO_SWEEP, 2 for the others, whose graphs hold thousands of
- *                 nodes) and replayed;
- *                 GRAPH is FUSED | CAPTURED.  Results never depend on the mode. */
+ *                 into HIP graphs (50 sweeps per graph for FUSED, 24 launches
+ *                 for TWO_SWEEP, 2 sweeps for the others, whose graphs hold
+ *                 thousands of nodes) and replayed.  FUSED | CAPTURED is the
+ *                 paper's captured form of strategy C, an exchange in every
+ *                 iteration.  Results never depend on the mode. */
 typedef enum {
     J3D_UNFUSED_BLOCK = 0,
     J3D_UNFUSED_PHASE = 1,
@@ -275,31 +277,29 @@ j3d_status j3d_batch_arena_bytes(int32_t count, const j3d_problem *probs, uint64
 
 /* Lay out `count` problems (each with its own decomposition, boundary and
  * seed) and their iteration counts iters[i] >= 0, and enqueue their seeded
- * initialisation.  tune: the kernel shape for every launch of the batch, as
- * resolved by the caller's autotuner from its tune cache (the cache itself,
- * a file of measured shapes per device and problem mix, is kept by the
- * caller, not parsed here); NULL picks the default shape.  EINVAL for count
+ * initialisation.  tune: the one-sweep kernel shape for every launch of the
+ * batch, as resolved by the caller's autotuner from its tune cache (the cache
+ * itself, a file of measured shapes per device and problem mix, is kept by the
+ * caller, not parsed here); NULL or {-1, 0, 0}: the library's choice, several
+ * sweeps per launch.  EINVAL for count
  * < 1, NULL arrays, a bad problem or a bad shape; ENOMEM if the arena is too
  * small; all before device work.                                            */
 j3d_status j3d_batch_create(int32_t count, const j3d_problem *probs, const int64_t *iters,
                             void *dev_arena, uint64_t arena_bytes, void *hip_stream,
                             const j3d_tune *tune, j3d_batch **out);
 
-/* Run every problem to its iteration count: step s is one launch covering
- * every tile of every problem with iters > s.  residuals_out (count doubles
+/* Run every problem to its iteration count: launch k covers every tile of
+ * every problem with iterations left and advances each by several sweeps (one
+ * sweep if a shape was passed as tune).  residuals_out (count doubles
  * or NULL) receives each problem's last-sweep residual; with it the call
  * synchronises.  A batch runs once; ESTATE afterwards.                       */
 j3d_status j3d_batch_run(j3d_batch *b, double *residuals_out);
 
-/* The same run with two sweeps per launch (the TWO_SWEEP scheme of j3d_run)
- * for batches whose problems are all undivided (one block each; EINVAL
- * otherwise, before any device work): problems with an odd count first take
- * one ordinary sweep in one launch over the batch, then launch k covers the
- * problems with more than k sweep pairs left, each advancing two sweeps.
- * Results and residuals are bit-identical to j3d_batch_run.  The batch's
- * tile shape from j3d_tune is used for the odd sweep only; the two-sweep
- * launches use 64 x 16 tiles and z-chunks of 32.  Not in the paper.  A batch
- * runs once, by either call; ESTATE afterwards.                              */
+/* The same run with several sweeps per launch whatever the batch's tune, for
+ * batches whose problems are all undivided (one block each; EINVAL otherwise,
+ * before any device work).  Results and residuals are bit-identical to
+ * j3d_batch_run.  Not in the paper.  A batch runs once, by either call;
+ * ESTATE afterwards.                                                         */
 j3d_status j3d_batch_run_two_sweep(j3d_batch *b, double *residuals_out);
 
 /* Copy problem i's interior to dst (dense).  Synchronises for host dst. */
@@ -357,18 +357,18 @@ j3d_status j3d_pool_step(j3d_pool *pl, int32_t sweeps);
 j3d_status j3d_pool_set_policy(j3d_pool *pl, int64_t fill_cells, int32_t max_wait_rounds,
                                int32_t backlog_share);
 
-/* Sweep kernel shape of the pool's rounds: variant (-1 keeps the default
+/* One-sweep kernel shape of the pool's rounds, which advance one sweep per
+ * launch then: variant (-1 keeps the default
  * flattened 512-thread tile) and zchunk (>= 1 planes per tile, default 32);
  * blocks_per_cu must be 0.
- * NULL restores the default.  ESTATE unless every slot is free (a request's
+ * NULL restores the default, several sweeps per launch.  ESTATE unless every
+ * slot is free (a request's
  * tile count is checked against the pool's tile table at admission).       */
 j3d_status j3d_pool_set_tune(j3d_pool *pl, const j3d_tune *t);
 
-/* enable 1: rounds advance requests two sweeps per launch (the TWO_SWEEP
- * scheme of j3d_run; every request is an undivided grid): a request whose
- * share of the round is odd takes one ordinary sweep first.  Results,
- * residuals and check points are unchanged (bit-identical).  enable 0: one
- * sweep per launch (the default).  Only while the pool is empty (ESTATE
+/* enable 1: rounds advance requests several sweeps per launch even after
+ * j3d_pool_set_tune.  Results, residuals and check points are unchanged
+ * (bit-identical).  enable 0: as j3d_pool_set_tune says (the default).  Only while the pool is empty (ESTATE
  * otherwise); EINVAL for other values.  Not in the paper.                  */
 j3d_status j3d_pool_set_two_sweep(j3d_pool *pl, int32_t enable);
 
@@ -405,7 +405,7 @@ j3d_status j3d_pool_destroy(j3d_pool *pl);
 
 /* For callers that cannot allocate device memory (code under stream capture,
  * tight serving loops, harnesses that forbid allocation): a one-shot solve of
- * problem p in FUSED mode (the j3d_run path) that calls no hipMalloc, hipFree,
+ * problem p by the launches of GRAPH mode that calls no hipMalloc, hipFree,
  * hipHostMalloc, stream, event or graph creation.
  *  fields        caller device memory, 256-byte aligned, of at least
  *                j3d_field_bytes(p) bytes (ENOMEM otherwise): the two iterates

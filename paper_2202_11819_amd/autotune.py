@@ -21,6 +21,8 @@ import torch
 from . import j3d
 from .api import Batch
 
+LIBRARY = (-1, 0, 0)  # the library's choice: several sweeps per launch
+
 DEFAULT_CACHE = os.path.join(os.path.expanduser("~"), ".cache", "j3d", "tune.json")
 
 
@@ -39,9 +41,10 @@ def device_arch() -> str:
 
 def candidates(problems):
     """Stage 1: every tile shape that suits the mix's widths, z-chunk 32, one
-    workgroup per tile."""
+    workgroup per tile; last, the library's own choice (several sweeps per launch)."""
     widest = max(p.n[0] for p in problems)
-    return [(v, 32, 0) for v, (tx, ty, threads) in enumerate(j3d.variants()) if tx <= max(64, 2 * widest)]
+    shapes = [(v, 32, 0) for v, (tx, ty, threads) in enumerate(j3d.variants()) if tx <= max(64, 2 * widest)]
+    return shapes + [LIBRARY]
 
 
 def refinements(best_shapes):
@@ -101,12 +104,13 @@ def tune_batch(problems, iters, sample_sweeps=24, cache_path=DEFAULT_CACHE, log=
                 continue
             res.append((dt, cand))
             if log:
-                log(f"[autotune] variant {cand[0]} {j3d.variants()[cand[0]]} zchunk {cand[1]} "
+                shape = j3d.variants()[cand[0]] if cand != LIBRARY else "library's choice"
+                log(f"[autotune] variant {cand[0]} {shape} zchunk {cand[1]} "
                     f"blocks/CU {cand[2]}: {dt * 1e3:.2f} ms")
         return sorted(res)
 
     stage1 = run(candidates(problems))
-    shapes = [c[0] for _, c in stage1[:keep]]
+    shapes = [c[0] for _, c in stage1 if c != LIBRARY][:keep]
     stage2 = run([c for c in refinements(shapes) if c[1] != 32 or c[2] != 0])
     results = sorted(stage1 + stage2)
     best = results[0][1]

@@ -21,6 +21,13 @@ j3d_status upload_tables(const Plan &plan, char *arena, hipStream_t stream);
 j3d_status upload_tiles(const Plan &plan, const std::vector<Tile> &tiles, char *arena,
                         hipStream_t stream);
 
+// Upload a plan's multi-sweep tiles (nothing to do without a shape).
+j3d_status upload_multi(const Plan &plan, const MultiPlan &m, char *arena, hipStream_t stream);
+
+// Launch arguments of a plan's multi-sweep launches: everything but the tiles
+// to run, the parity and the sweep count.
+MultiArgs multi_args(const Plan &plan, char *arena);
+
 // Seeded initialisation of every problem of a plan (interior of parity 0,
 // halo storage of both parities).
 j3d_status init_fields(const Plan &plan, char *arena, hipStream_t stream);

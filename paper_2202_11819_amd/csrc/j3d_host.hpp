@@ -56,6 +56,7 @@ struct Plan {
     std::vector<ProbPlan> probs;
     bool with_sr = true;          // send/receive buffers of the unfused modes
     uint64_t off_blocks = 0, off_probs = 0, off_tiles = 0, off_res = 0, off_queue = 0;
+    uint64_t off_mtiles = 0, mtiles_cap = 0;  // tiles of the multi-sweep launches
     uint64_t off_bounce = 0, bounce_doubles = 0;
     uint64_t tiles_cap = 0;
     uint64_t total = 0;           // arena bytes
@@ -160,6 +161,37 @@ inline void tiles_xy(const VariantInfo &vi, int64_t ex, int64_t ey, int64_t *ntx
         *nty = (ey + vi.tile_y - 1) / vi.tile_y;
     }
 }
+
+// ---- several sweeps per launch --------------------------------------------------
+
+// The multi-sweep tiles of a set of problems: shape < 0 when the one-sweep
+// launches have to serve.
+struct MultiPlan {
+    int shape = -1;
+    int t = 1;             // sweeps per launch
+    bool general = false;  // blocks of unequal extents: per-lane plane strides
+    std::vector<Tile> tiles;
+    std::vector<uint64_t> work;
+    std::vector<int32_t> prefix;  // tiles of the first k problems of `order`
+};
+
+struct Piece {
+    int32_t at, len;
+};
+// Cuts [0, n) into near-equal pieces that fit `cap` lanes or rows with their
+// halo (T cells, or the one boundary cell at the ends of the axis); starts
+// are multiples of `align`.
+void cut_axis(int32_t n, int cap, int t, int align, std::vector<Piece> *out);
+
+// Shape and tiles for problems order[0], order[1], ... of the plan (all in table
+// order if order is NULL), chosen by estimated time; at most `cap` tiles.
+// m->shape stays -1 where the one-sweep launches have to serve: a tile's blocks
+// lie further apart than a 32-bit offset reaches, or unequal blocks are
+// shallower than the sweeps of a launch.
+void make_multi(const Plan &plan, const std::vector<int32_t> *order, int cus, uint64_t cap, MultiPlan *m);
+
+// Problem descriptor of a plan's problem (sweeps 0 .. iters).
+void fill_prob(const Plan &plan, int32_t i, int64_t maps_base, ProbDesc *pd);
 
 // Validates a tune against a plan; fills the effective z-chunk.
 j3d_status check_tune(const Plan &plan, const j3d_tune *t, int *zchunk_eff);

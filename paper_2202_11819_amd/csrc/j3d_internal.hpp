@@ -74,8 +74,9 @@ struct ProbDesc {           // 64 bytes
     int32_t check_every;    // residual every k-th sweep (0: only at `limit`)
     int32_t res_slot;       // index of the problem's residual word
     int32_t flags;          // PF_RES_LAST: evaluate the residual at `limit`
-    int32_t pad0;
-    int64_t pad[4];
+    int32_t nb[3];          // multi-sweep launches: blocks per axis,
+    int32_t n[3];           // interior cells per axis,
+    int64_t maps_off;       // per-axis maps (bytes from MultiArgs::maps; unused for one block)
 };
 static_assert(sizeof(ProbDesc) == 64, "ProbDesc layout");
 
@@ -182,34 +183,41 @@ constexpr int flat_x0(int ex, int tnx, int tx)
     return tx == 0 ? 0 : tx >= tnx ? ex : (int)(((int64_t)tx * ex / tnx) & ~(int64_t)15);
 }
 
-// Two sweeps per launch on grids of one block (j3d_twostep.hip).  A launch
-// reads iterate t from one buffer and writes iterate t+2 to the other; x-y
-// tiles of 64 x 16 cells (512 threads), z cut into near-equal pieces.
-// Single grid: blocks == nullptr, the fields below `blocks` are unused.
-// Multi-problem (batched) launch: tile_count tiles from tiles[tile_begin..];
-// a tile's problem takes part while step < limit, reading buffer
-// (base + step) & 1, and adds its residual when step + 1 == limit (ProbDesc
-// counts launches here, not sweeps).
-struct TwoStepArgs {
-    const double *cur;        // field of iterate t (plane index 0: the z- ghost plane)
-    double *nxt;              // field that receives iterate t+2
-    const double *xh;         // x-halo arrays (x- then x+, ey*ez each, y fastest)
-    unsigned long long *res;  // residual word(s) of the second sweep (bit pattern)
-    int32_t ex, ey, ez, pitch;
-    int32_t ntx, nty, ntz;
-    int32_t want_res;
-    const BlockDesc *blocks;  // multi-problem launch only
-    const ProbDesc *probs;
+// ---- several sweeps per launch (j3d_multisweep.hip) ----------------------------
+// A launch reads an iterate from one buffer and writes the iterate up to T
+// sweeps later to the other.  Its tiles are rectangles of the problem's grid
+// (global coordinates; Tile::block is the problem's first block), read across
+// block boundaries.
+//   plain launch: nsweeps (1..T) sweeps from buffer `parity`;
+//   MS_MULTI: launch number `step` of a sequence.  A problem with `limit` sweeps
+//   takes part while step * T < limit, in buffer (base + step) & 1, and adds
+//   its residual with its last sweep (PF_RES_LAST).
+enum : int32_t { MS_MULTI = 1, MS_RES = 2 };
+
+struct MultiArgs {
     const Tile *tiles;
-    double *base;
+    int32_t tile_begin;
+    int32_t xcut[kXcdCount + 1];  // tile runs per XCD, as in SweepArgs
+    int32_t tile_count, parity, nsweeps, flags;
+    double *base;                 // arena base
+    const BlockDesc *blocks;
+    const ProbDesc *probs;
+    const char *maps;             // ProbDesc::maps_off counts from here
+    const char *end;              // end of the memory that holds the fields
+    unsigned long long *res;
     int64_t step;
-    int32_t tile_begin, tile_count, zchunk;
 };
-// Tile counts for a block and z-chunk (0 or >= ez: whole planes); returns the total.
-int twostep_tiles(int ex, int ey, int ez, int zchunk, int *ntx, int *nty, int *ntz);
-// Tiles of blocks b0..b1-1 for a multi-problem launch with z-chunks of zchunk planes.
-void twostep_make_tiles(const BlockDesc *blocks, int32_t b0, int32_t b1, int zchunk, std::vector<Tile> *tiles);
-int launch_twostep(const TwoStepArgs &a, void *stream);
+
+// A compiled shape: rows of lanes a tile has along y (64 along x), sweeps per
+// launch, threads, planes of its register ring, workgroups per compute unit.
+struct MShapeInfo {
+    int rows, t, threads, ring, per_cu;
+};
+constexpr int kMultiSegs = 3;  // block rows along z that a tile of unequal blocks may read
+int mshape_count();
+MShapeInfo mshape_info(int i);
+// general: some problem's blocks differ in extents.
+int launch_multisweep(int shape, bool general, const MultiArgs &a, int grid, void *stream);
 
 // ---- launchers (defined in j3d_kernels.hip); all enqueue on `stream` ----------
 // Every launcher returns 0 or a hipError_t value.

@@ -1,8 +1,8 @@
 // j3d_noalloc.hip -- a solve that allocates no device memory.
 //
-// j3d_solve_noalloc runs the fused sweep of j3d_run (strategy C, one launch
-// per iteration for all blocks) on fields that live in memory the caller
-// passes, and keeps everything else it needs on the device (block and
+// j3d_solve_noalloc runs the launches of j3d_run (several sweeps each; where
+// their tables do not fit the scratch, the fused sweep, one launch per
+// iteration for all blocks) on fields that live in memory the caller passes, and keeps everything else it needs on the device (block and
 // problem descriptors, the tile table, the per-axis maps of the dense
 // copies, the residual word) in one file-scope device array of fixed size.
 // It is for callers that cannot allocate: code under stream capture, tight
@@ -159,7 +159,7 @@ extern "C" j3d_status j3d_solve_noalloc(const j3d_problem *p, void *fields, uint
                 maps.push_back(b);
                 maps.push_back((int32_t)l);
             }
-    const Layout lay = scratch_layout(plan.blocks.size(), tiles.size(), maps.size());
+    Layout lay = scratch_layout(plan.blocks.size(), tiles.size(), maps.size());
     if (lay.total > kScratchBytes)
         return set_error(J3D_EINVAL, "problem needs %llu bytes of tables (%zu blocks, %zu tiles), more than the %llu "
                          "of the static scratch", (unsigned long long)lay.total, plan.blocks.size(), tiles.size(),
@@ -167,13 +167,21 @@ extern "C" j3d_status j3d_solve_noalloc(const j3d_problem *p, void *fields, uint
     char *scr = nullptr;
     st = scratch_address(dev, &scr);
     if (st != J3D_OK) return st;
+    // several sweeps per launch if their tile table fits as well
+    MultiPlan multi;
+    make_multi(plan, nullptr, cus, kScratchBytes / sizeof(Tile), &multi);
+    const Layout mlay = scratch_layout(plan.blocks.size(), multi.tiles.size(), maps.size());
+    const bool many = multi.shape >= 0 && mlay.total <= kScratchBytes;
+    if (many) {
+        tiles = std::move(multi.tiles);
+        lay = mlay;
+    }
 
     // ---- tables into the scratch (the host copies are consumed before return) ----
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     ProbDesc prob;
-    std::memset(&prob, 0, sizeof prob);
+    fill_prob(plan, 0, (int64_t)pp.maps_off, &prob);
     prob.limit = iters;
-    prob.flags = PF_RES_LAST;
     st = hip_status(hipMemcpyAsync(scr + lay.off_blocks, plan.blocks.data(), plan.blocks.size() * sizeof(BlockDesc),
                                    hipMemcpyHostToDevice, stream),
                     "table upload");
@@ -209,7 +217,7 @@ extern "C" j3d_status j3d_solve_noalloc(const j3d_problem *p, void *fields, uint
     if (st == J3D_OK && interior_in)
         st = hip_status(launch_scatter(base, dblocks, 0, pp.d.nb, dmaps, n, 0, n[2], interior_in, 0, stream),
                         "scatter launch");
-    if (st == J3D_OK && nb > 1) {
+    if (st == J3D_OK && nb > 1 && !many) {
         hipLaunchKernelGGL(xhalo_pull_kernel, dim3((unsigned)std::min<int64_t>((maxx + 255) / 256, 1024),
                                                    (unsigned)std::min<int32_t>(nb, 65535)),
                            dim3(256), 0, stream, base, dblocks, nb, 0);
@@ -218,7 +226,30 @@ extern "C" j3d_status j3d_solve_noalloc(const j3d_problem *p, void *fields, uint
     if (st == J3D_OK && residual_out)
         st = hip_status(launch_fill_u64(res, 1, 0ull, stream), "residual reset");
 
-    // ---- iterations: one fused launch each (strategy C for all blocks) ----
+    // ---- iterations: several per launch ----
+    int parity = 0;
+    int64_t done = 0;
+    if (many) {
+        MultiArgs m;
+        std::memset(&m, 0, sizeof m);
+        m.base = base;
+        m.end = static_cast<const char *>(fields) + o * sizeof(double);
+        m.blocks = dblocks;
+        m.probs = reinterpret_cast<const ProbDesc *>(scr + lay.off_probs);
+        m.tiles = reinterpret_cast<const Tile *>(scr + lay.off_tiles);
+        m.maps = scr + lay.off_maps;
+        m.res = res;
+        m.tile_count = (int32_t)tiles.size();
+        const int grid = xcd_split(multi.work, 0, m.tile_count, m.xcut);
+        for (; done < iters && st == J3D_OK; parity ^= 1) {
+            m.nsweeps = (int32_t)std::min<int64_t>(multi.t, iters - done);
+            done += m.nsweeps;
+            m.parity = parity;
+            m.flags = residual_out && done == iters ? MS_RES : 0;
+            st = hip_status(launch_multisweep(multi.shape, multi.general, m, grid, stream), "multi-sweep launch");
+        }
+    }
+    // ---- or one fused launch each (strategy C for all blocks) ----
     SweepArgs a;
     std::memset(&a, 0, sizeof a);
     a.base = base;
@@ -230,13 +261,13 @@ extern "C" j3d_status j3d_solve_noalloc(const j3d_problem *p, void *fields, uint
     for (const BlockDesc &B : plan.blocks) ezm = std::max(ezm, B.ext[2]);
     a.zchunk = t.zchunk > 0 ? t.zchunk : ezm;
     a.tile_count = (int32_t)tiles.size();
-    for (int64_t k = 0; k < iters && st == J3D_OK; ++k) {
-        a.parity = (int32_t)(k & 1);
-        a.flags = SW_FUSED | (residual_out && k + 1 == iters ? SW_RES : 0);
+    for (; done < iters && st == J3D_OK; ++done, parity ^= 1) {
+        a.parity = parity;
+        a.flags = SW_FUSED | (residual_out && done + 1 == iters ? SW_RES : 0);
         st = hip_status(launch_sweep(t.variant, a, a.tile_count, stream), "sweep launch");
     }
     if (st == J3D_OK)
-        st = hip_status(launch_gather(base, dblocks, 0, pp.d.nb, dmaps, n, 0, n[2], interior_out, (int)(iters & 1),
+        st = hip_status(launch_gather(base, dblocks, 0, pp.d.nb, dmaps, n, 0, n[2], interior_out, parity,
                                       stream),
                         "gather launch");
     if (st != J3D_OK) return st;

@@ -206,6 +206,230 @@ uint64_t count_tiles(const Plan &plan, int variant, int zchunk)
     return n;
 }
 
+void cut_axis(int32_t n, int cap, int t, int align, std::vector<Piece> *out)
+{
+    out->clear();
+    const int inner = cap - 2 * t, end = cap - t - 1;
+    int m = n <= cap - 2 ? 1 : n <= 2 * end ? 2 : 2 + (n - 2 * end + inner - 1) / inner;
+    for (;; ++m) {
+        out->clear();
+        bool ok = true;
+        int32_t at = 0;
+        for (int i = 0; i < m && ok; ++i) {
+            int32_t next = n;
+            if (i + 1 < m) {
+                // the end pieces hold t - 1 cells more: they need no ring there
+                next = (int32_t)((int64_t)(i + 1) * (n + 2 * (t - 1)) / m) - (t - 1);
+                next = (next + align / 2) / align * align;
+            }
+            const int32_t len = next - at;
+            ok = len >= 1 && len + std::min(t, at + 1) + std::min(t, n - next + 1) <= cap;
+            out->push_back({at, len});
+            at = next;
+        }
+        if (ok) return;
+    }
+}
+
+namespace {
+
+constexpr int kMinMultiZ = 4;
+
+int x_align(const ProbPlan &pp)
+{
+    for (int64_t e : pp.d.ext[0])
+        if (e % 8) return 1;
+    return 8;
+}
+
+uint64_t multi_tiles_bound(const Plan &plan)
+{
+    uint64_t best = 0;
+    std::vector<Piece> px, py;
+    for (int s = 0; s < mshape_count(); ++s) {
+        const MShapeInfo mi = mshape_info(s);
+        uint64_t n = 0;
+        for (const ProbPlan &pp : plan.probs) {
+            cut_axis((int32_t)pp.d.n[0], 64, mi.t, x_align(pp), &px);
+            cut_axis((int32_t)pp.d.n[1], mi.rows, mi.t, 1, &py);
+            n += px.size() * py.size() * (uint64_t)ceil_div(pp.d.n[2], kMinMultiZ);
+        }
+        best = std::max(best, n);
+    }
+    return best;
+}
+
+// Plane steps of a tile: its planes, the ramp on both sides, whole rounds of
+// the register ring.
+int64_t multi_steps(const MShapeInfo &mi, int64_t planes)
+{
+    return ceil_div(planes + 2 * mi.t, mi.ring) * mi.ring;
+}
+
+// Estimated microseconds per sweep of a launch of `tiles` tiles of `steps`
+// plane steps each.  Fitted to MI355X timings of every shape on 13 grids from
+// 33x35x31 to 1024^3 (within 15% of the fastest shape's time on each):
+//   - a plane step issues about 13 instructions per cell, stage and wave
+//     (7 FP64, 4 DPP, 2 for the boundary) and 15 more, 1.8 ns each per SIMD,
+//     and waits about 0.3 us for LDS, barrier and dependent chains;
+//   - a tile starts with about 3 us of table lookups and first loads;
+//   - memory moves 17 bytes per cell and launch at 5.3 TB/s, at 3.2 TB/s where
+//     tiles end inside cache lines and the grid is past the last-level cache;
+//   - the two overlap only in part: the third root of the sum of cubes.
+double multi_cost(const MShapeInfo &mi, int cus, double tiles, double steps, double cells, bool ragged)
+{
+    const double c = std::min<double>(mi.per_cu, std::ceil(tiles / cus));  // workgroups sharing a compute unit
+    const int cpt = mi.rows * 64 / mi.threads;                             // cells per thread
+    const double valu = mi.threads / 256 * (cpt * mi.t * 13.0 + 15) * 0.0018;
+    const double step = c * valu + 0.3;
+    const double compute = std::ceil(tiles / (cus * c)) * (steps * step + 3.0);
+    const double hbm = cells * 17.0 / (ragged && cells > 1.6e7 ? 3.2e6 : 5.3e6);
+    return (std::cbrt(compute * compute * compute + hbm * hbm * hbm) + 3.0) / mi.t;
+}
+
+// Byte span of a tile's blocks from its first block's field: the lane offsets
+// are 32-bit.
+bool multi_span_ok(const Plan &plan, const ProbPlan &pp, const std::vector<Piece> &px, const std::vector<Piece> &py,
+                   int t)
+{
+    const Decomp &d = pp.d;
+    if (pp.nblocks == 1) return true;
+    auto owner = [](const std::vector<int64_t> &org, int64_t c) {
+        return (int32_t)(std::upper_bound(org.begin(), org.end(), c) - org.begin()) - 1;
+    };
+    for (const Piece &y : py)
+        for (const Piece &x : px) {
+            const int32_t ax = owner(d.org[0], std::max(0, x.at - t)), ay = owner(d.org[1], std::max(0, y.at - t));
+            const int32_t ex = owner(d.org[0], std::min<int64_t>(d.n[0] - 1, x.at + x.len - 1 + t));
+            const int32_t ey = owner(d.org[1], std::min<int64_t>(d.n[1] - 1, y.at + y.len - 1 + t));
+            for (int32_t bz = 0; bz < d.nb[2]; ++bz) {
+                const BlockDesc &A = plan.blocks[pp.block_begin + ax + d.nb[0] * (ay + d.nb[1] * bz)];
+                const BlockDesc &B = plan.blocks[pp.block_begin + ex + d.nb[0] * (ey + d.nb[1] * bz)];
+                const int64_t end = B.off[0] - A.off[0] + block_field_cells(B.ext[0], B.ext[1], B.ext[2]);
+                if (end * 8 > 0xFFFFF000ll) return false;
+            }
+        }
+    return true;
+}
+
+}  // namespace
+
+void fill_prob(const Plan &plan, int32_t i, int64_t maps_base, ProbDesc *pd)
+{
+    std::memset(pd, 0, sizeof *pd);
+    const ProbPlan &pp = plan.probs[i];
+    pd->res_slot = i;
+    pd->limit = pp.iters;
+    pd->flags = PF_RES_LAST;
+    for (int a = 0; a < 3; ++a) {
+        pd->nb[a] = pp.d.nb[a];
+        pd->n[a] = (int32_t)pp.d.n[a];
+    }
+    pd->maps_off = (int64_t)pp.maps_off - maps_base;
+}
+
+namespace {
+
+// z pieces of a problem: near-equal, at most zc planes.  With unequal blocks
+// (general) each lies in one block row, and the rows are at least t deep, so a
+// tile reads its own row and its two neighbours at most.
+bool cut_z(const ProbPlan &pp, bool general, int t, int zc, std::vector<Piece> *out)
+{
+    out->clear();
+    const bool rows = general && pp.nblocks > 1;
+    for (int32_t b = 0; b < (rows ? pp.d.nb[2] : 1); ++b) {
+        const int64_t at = rows ? pp.d.org[2][b] : 0, len = rows ? pp.d.ext[2][b] : pp.d.n[2];
+        if (rows && len < t) return false;
+        const int64_t n = ceil_div(len, zc);
+        for (int64_t i = 0; i < n; ++i)
+            out->push_back({(int32_t)(at + i * len / n), (int32_t)((i + 1) * len / n - i * len / n)});
+    }
+    return true;
+}
+
+}  // namespace
+
+void make_multi(const Plan &plan, const std::vector<int32_t> *order, int cus, uint64_t cap, MultiPlan *m)
+{
+    m->shape = -1;
+    m->general = false;
+    m->tiles.clear();
+    m->prefix.assign(1, 0);
+    const int32_t count = (int32_t)(order ? order->size() : plan.probs.size());
+    auto prob = [&](int32_t k) -> const ProbPlan & { return plan.probs[order ? (*order)[k] : k]; };
+    int64_t depth = 1;
+    double cells = 0;
+    bool ragged = false;
+    for (int32_t k = 0; k < count; ++k) {
+        const ProbPlan &pp = prob(k);
+        const BlockDesc &A = plan.blocks[pp.block_begin];
+        for (int32_t b = pp.block_begin; b < pp.block_begin + pp.nblocks; ++b)
+            for (int a = 0; a < 3; ++a) m->general = m->general || plan.blocks[b].ext[a] != A.ext[a];
+        depth = std::max(depth, pp.d.n[2]);
+        ragged = ragged || x_align(pp) == 1;
+        cells += (double)pp.d.n[0] * pp.d.n[1] * pp.d.n[2];
+    }
+    std::vector<Piece> px, py, pz;
+    int best_shape = -1, best_zc = 0;
+    double best = 0;
+    for (int s = 0; s < mshape_count(); ++s) {
+        const MShapeInfo mi = mshape_info(s);
+        std::vector<int64_t> xy(count);
+        bool ok = true;
+        for (int32_t k = 0; k < count && ok; ++k) {
+            const ProbPlan &pp = prob(k);
+            cut_axis((int32_t)pp.d.n[0], 64, mi.t, x_align(pp), &px);
+            cut_axis((int32_t)pp.d.n[1], mi.rows, mi.t, 1, &py);
+            xy[k] = (int64_t)px.size() * (int64_t)py.size();
+            ok = multi_span_ok(plan, pp, px, py, mi.t);
+        }
+        int last_zc = 0;
+        for (int64_t nc = 1; ok && nc <= ceil_div(depth, kMinMultiZ); nc += 1 + nc / 16) {
+            const int zc = (int)ceil_div(depth, nc);
+            if (zc == last_zc) continue;
+            last_zc = zc;
+            double tiles = 0, steps = 0;
+            for (int32_t k = 0; k < count && ok; ++k) {
+                ok = cut_z(prob(k), m->general, mi.t, zc, &pz);
+                tiles += (double)xy[k] * pz.size();
+                for (const Piece &z : pz) steps += (double)xy[k] * multi_steps(mi, z.len);
+            }
+            if (!ok || tiles > (double)cap) break;
+            const double cost = multi_cost(mi, cus, tiles, steps / tiles, cells, ragged);
+            if (best_shape < 0 || cost < best) {
+                best = cost;
+                best_shape = s;
+                best_zc = zc;
+            }
+        }
+    }
+    if (best_shape < 0) return;
+    const MShapeInfo mi = mshape_info(best_shape);
+    for (int32_t k = 0; k < count; ++k) {
+        const ProbPlan &pp = prob(k);
+        cut_axis((int32_t)pp.d.n[0], 64, mi.t, x_align(pp), &px);
+        cut_axis((int32_t)pp.d.n[1], mi.rows, mi.t, 1, &py);
+        cut_z(pp, m->general, mi.t, best_zc, &pz);
+        for (const Piece &z : pz)
+            for (const Piece &y : py)
+                for (const Piece &x : px) {
+                    Tile t{};
+                    t.block = pp.block_begin;
+                    t.x0 = x.at;
+                    t.nxv = x.len;
+                    t.y0 = y.at;
+                    t.nyv = y.len;
+                    t.z0 = z.at;
+                    t.nzv = z.len;
+                    m->tiles.push_back(t);
+                }
+        m->prefix.push_back((int32_t)m->tiles.size());
+    }
+    tile_work(m->tiles, &m->work);
+    m->shape = best_shape;
+    m->t = mi.t;
+}
+
 j3d_status make_plan(int32_t count, const j3d_problem *probs, bool with_sr, Plan *plan)
 {
     if (count < 1 || !probs) return set_error(J3D_EINVAL, "need at least one problem");
@@ -264,6 +488,8 @@ j3d_status make_plan(int32_t count, const j3d_problem *probs, bool with_sr, Plan
     for (int v = 0; v < variant_count(); ++v) cap = std::max(cap, count_tiles(*plan, v, kMinZchunk));
     plan->tiles_cap = cap;
     plan->off_tiles = bump.take(cap * sizeof(Tile));
+    plan->mtiles_cap = multi_tiles_bound(*plan);
+    plan->off_mtiles = bump.take(plan->mtiles_cap * sizeof(Tile));
     for (ProbPlan &pp : plan->probs)
         pp.maps_off = bump.take((uint64_t)(pp.d.n[0] + pp.d.n[1] + pp.d.n[2]) * 2 * sizeof(int32_t));
     plan->off_res = bump.take((uint64_t)(count + 1) * sizeof(uint64_t));

@@ -25,7 +25,6 @@ namespace {
 // 64x32 tiles of 256 threads and 32-plane z-chunks: enough workgroups per
 // request that a round of a few mid-sized requests fills the GPU
 constexpr int kPoolZchunk = 32;
-constexpr int kPoolTwoZchunk = 64;  // z-chunk of the two-sweep rounds
 constexpr int64_t kPoolTilesPerReq = 4096;
 
 enum ReqState { R_FREE = 0, R_RUNNING, R_COPYING, R_DONE, R_REPORTED };
@@ -122,11 +121,8 @@ struct j3d_pool {
     int64_t fill_cells = int64_t(1) << 25;
     int32_t max_wait = 32;
     int32_t backlog_share = 2;  // > 0: the target is at least 1/backlog_share of the running cells
-    // two sweeps per launch: tables of the pair launches (page-locked, apart
-    // from the single-sweep ones, which are still in flight when these are filled)
-    bool two_sweep = false;
-    ProbDesc *host_probs2 = nullptr;
-    Tile *host_tiles2 = nullptr;
+    bool tuned = false;      // one-sweep shape set by the caller: rounds keep to it
+    bool two_sweep = false;  // several sweeps per launch asked for, whatever the shape
 };
 
 namespace {
@@ -300,10 +296,8 @@ j3d_status j3d_pool_admit(j3d_pool *pl, const j3d_problem *p, int64_t max_iters,
     int64_t ntx, nty;
     tiles_xy(vi, d.n[0], d.n[1], &ntx, &nty);
     const int64_t tiles = ntx * nty * ((d.n[2] + pl->zchunk - 1) / pl->zchunk);
-    int tx2 = 0, ty2 = 0, tz2 = 0;
-    const int64_t tiles2 = pl->two_sweep ? twostep_tiles((int)d.n[0], (int)d.n[1], (int)d.n[2], kPoolTwoZchunk,
-                                                         &tx2, &ty2, &tz2)
-                                         : 0;
+    // with several sweeps per launch asked for, 64 x 16 columns of 64 planes bound the request as well
+    const int64_t tiles2 = pl->two_sweep ? ((d.n[0] + 63) / 64) * ((d.n[1] + 15) / 16) * ((d.n[2] + 63) / 64) : 0;
     if (tiles > kPoolTilesPerReq || tiles2 > kPoolTilesPerReq)
         return set_error(J3D_EINVAL, "request of %lldx%lldx%lld needs %lld tiles, more than %lld",
                          (long long)d.n[0], (long long)d.n[1], (long long)d.n[2],
@@ -420,54 +414,63 @@ j3d_status j3d_pool_step(j3d_pool *pl, int32_t sweeps)
         r.waited = chosen[c.slot] ? 0 : r.waited + 1;
     }
     // Per chosen request: k sweeps this round (up to its next residual check).
-    // One sweep per launch: step j advances every request with j < k.  Two
-    // sweeps per launch: a request with odd k first takes one ordinary sweep
-    // (one launch for the round), then k / 2 two-sweep launches; descriptors
-    // then carry buffer parities instead of sweep counts.
-    std::vector<Tile> tiles2;
-    bool any_odd = false;
-    int64_t max_pairs = 0;
+    // Several sweeps per launch: launch j advances every request with more
+    // than j * t sweeps to go; its descriptor counts this round's sweeps and
+    // names the buffer that holds its current iterate.
+    Plan round;  // the chosen requests as problems of one plan
     for (int32_t s = 0; s < pl->max_slots; ++s) {
         Req &r = pl->reqs[s];
         if (r.state != R_RUNNING || !chosen[s]) continue;
+        ProbPlan pp;
+        for (int a = 0; a < 3; ++a) {
+            pp.d.n[a] = r.n[a];
+            pp.d.nb[a] = 1;
+            pp.d.ext[a].assign(1, r.n[a]);
+            pp.d.org[a].assign(1, 0);
+        }
+        pp.block_begin = (int32_t)round.blocks.size();
+        pp.nblocks = 1;
+        round.blocks.push_back(r.blk);
+        round.probs.push_back(std::move(pp));
+    }
+    if (round.probs.empty()) return J3D_OK;
+    MultiPlan multi;
+    if (!pl->tuned || pl->two_sweep)
+        make_multi(round, nullptr, pl->cus, (uint64_t)pl->max_slots * kPoolTilesPerReq, &multi);
+    const bool many = multi.shape >= 0;
+    int64_t longest = 0;
+    for (const BlockDesc &B : round.blocks) {
+        const int32_t s = B.prob;
+        Req &r = pl->reqs[s];
         const int64_t base = r.iters_done;
         int64_t limit = r.max_iters;
         if (r.check_every > 0) limit = std::min(limit, (base / r.check_every + 1) * r.check_every);
         const int64_t k = std::max<int64_t>(0, std::min<int64_t>(sweeps, limit - base));
+        longest = std::max(longest, k);
         ProbDesc &pd = pl->host_probs[s];
         std::memset(&pd, 0, sizeof pd);
         pd.res_slot = s;
-        int newbuf;
-        if (!pl->two_sweep) {
-            pd.base = base;
-            pd.limit = limit;
-            pd.flags = PF_RES_LAST;
-            newbuf = (int)((base + k) & 1);
-        } else {
-            pd.base = r.buf;
-            pd.limit = r.buf + (k & 1);
-            pd.flags = k == 1 ? PF_RES_LAST : 0;
-            ProbDesc &q = pl->host_probs2[s];
-            std::memset(&q, 0, sizeof q);
-            q.base = r.buf ^ (int)(k & 1);
-            q.limit = k / 2;
-            q.res_slot = s;
-            newbuf = r.buf ^ (int)(k & 1) ^ (int)((k / 2) & 1);
-            any_odd = any_odd || (k & 1) != 0;
-            max_pairs = std::max<int64_t>(max_pairs, k / 2);
-            const size_t at = tiles2.size();
-            twostep_make_tiles(&r.blk, 0, 1, kPoolTwoZchunk, &tiles2);
-            for (size_t i = at; i < tiles2.size(); ++i) tiles2[i].block = s;
+        pd.base = r.buf;
+        pd.limit = many ? k : r.buf + k;
+        pd.flags = base + k == limit ? PF_RES_LAST : 0;
+        for (int a = 0; a < 3; ++a) {
+            pd.nb[a] = 1;
+            pd.n[a] = (int32_t)r.n[a];
         }
-        pl->round.push_back(RoundEntry{s, r.gen, base, limit, newbuf});
-        Plan one;
-        one.blocks.assign(1, r.blk);
-        std::vector<Tile> t;
-        make_tiles(one, 0, 1, pl->variant, pl->zchunk, &t, nullptr);
-        for (Tile &x : t) x.block = s;
-        tiles.insert(tiles.end(), t.begin(), t.end());
+        const int64_t flips = many ? (k + multi.t - 1) / multi.t : k;
+        pl->round.push_back(RoundEntry{s, r.gen, base, limit, r.buf ^ (int)(flips & 1)});
+        if (!many) {
+            Plan one;
+            one.blocks.assign(1, B);
+            const size_t at = tiles.size();
+            make_tiles(one, 0, 1, pl->variant, pl->zchunk, &tiles, nullptr);
+            for (size_t i = at; i < tiles.size(); ++i) tiles[i].block = s;
+        }
     }
-    if (pl->round.empty()) return J3D_OK;
+    if (many) {
+        tiles = std::move(multi.tiles);
+        for (Tile &t : tiles) t.block = round.blocks[t.block].prob;
+    }
     std::memcpy(pl->host_tiles, tiles.data(), tiles.size() * sizeof(Tile));
     j3d_status st = hip_status(hipMemcpyAsync(pl->arena + pl->lay.off_probs, pl->host_probs,
                                               pl->max_slots * sizeof(ProbDesc), hipMemcpyHostToDevice, pl->stream),
@@ -478,40 +481,33 @@ j3d_status j3d_pool_step(j3d_pool *pl, int32_t sweeps)
                         "round upload");
     unsigned long long *res = reinterpret_cast<unsigned long long *>(pl->arena + pl->lay.off_res);
     if (st == J3D_OK) st = hip_status(launch_fill_u64(res, pl->max_slots, 0ull, pl->stream), "residual reset");
-    SweepArgs a = pool_args(pl);
-    a.tile_begin = 0;
-    a.tile_count = (int32_t)tiles.size();
-    std::vector<uint64_t> work;
-    tile_work(tiles, &work);
-    const int grid = xcd_split(work, 0, a.tile_count, a.xcut);
-    const int32_t one_sweep_launches = pl->two_sweep ? (any_odd ? 1 : 0) : sweeps;
-    for (int32_t j = 0; j < one_sweep_launches && st == J3D_OK; ++j) {
-        a.step = j;
-        st = hip_status(launch_sweep(pl->variant, a, grid, pl->stream), "round sweep");
-    }
-    if (st == J3D_OK && max_pairs > 0) {
-        // the pair launches' tables replace the single sweep's, in stream order
-        std::memcpy(pl->host_tiles2, tiles2.data(), tiles2.size() * sizeof(Tile));
-        st = hip_status(hipMemcpyAsync(pl->arena + pl->lay.off_probs, pl->host_probs2,
-                                       pl->max_slots * sizeof(ProbDesc), hipMemcpyHostToDevice, pl->stream),
-                        "round upload");
-        if (st == J3D_OK)
-            st = hip_status(hipMemcpyAsync(pl->arena + pl->lay.off_tiles, pl->host_tiles2,
-                                           tiles2.size() * sizeof(Tile), hipMemcpyHostToDevice, pl->stream),
-                            "round upload");
-        TwoStepArgs a2;
-        std::memset(&a2, 0, sizeof a2);
-        a2.base = reinterpret_cast<double *>(pl->arena);
-        a2.blocks = reinterpret_cast<const BlockDesc *>(pl->arena + pl->lay.off_blocks);
-        a2.probs = reinterpret_cast<const ProbDesc *>(pl->arena + pl->lay.off_probs);
-        a2.tiles = reinterpret_cast<const Tile *>(pl->arena + pl->lay.off_tiles);
-        a2.res = res;
-        a2.zchunk = kPoolTwoZchunk;
-        a2.tile_begin = 0;
-        a2.tile_count = (int32_t)tiles2.size();
-        for (int64_t s2 = 0; s2 < max_pairs && st == J3D_OK; ++s2) {
-            a2.step = s2;
-            st = hip_status(launch_twostep(a2, pl->stream), "round two-sweep launch");
+    if (many) {
+        MultiArgs a;
+        std::memset(&a, 0, sizeof a);
+        a.base = reinterpret_cast<double *>(pl->arena);
+        a.blocks = reinterpret_cast<const BlockDesc *>(pl->arena + pl->lay.off_blocks);
+        a.probs = reinterpret_cast<const ProbDesc *>(pl->arena + pl->lay.off_probs);
+        a.tiles = reinterpret_cast<const Tile *>(pl->arena + pl->lay.off_tiles);
+        a.maps = pl->arena;
+        a.end = pl->arena + pl->arena_bytes;
+        a.res = res;
+        a.flags = MS_MULTI;
+        a.tile_count = (int32_t)tiles.size();
+        const int grid = xcd_split(multi.work, 0, a.tile_count, a.xcut);
+        for (int64_t j = 0; j * multi.t < longest && st == J3D_OK; ++j) {
+            a.step = j;
+            st = hip_status(launch_multisweep(multi.shape, multi.general, a, grid, pl->stream), "round launch");
+        }
+    } else {
+        SweepArgs a = pool_args(pl);
+        a.tile_begin = 0;
+        a.tile_count = (int32_t)tiles.size();
+        std::vector<uint64_t> work;
+        tile_work(tiles, &work);
+        const int grid = xcd_split(work, 0, a.tile_count, a.xcut);
+        for (int64_t j = 0; j < longest && st == J3D_OK; ++j) {
+            a.step = j;
+            st = hip_status(launch_sweep(pl->variant, a, grid, pl->stream), "round sweep");
         }
     }
     if (st == J3D_OK)
@@ -638,6 +634,7 @@ j3d_status j3d_pool_set_tune(j3d_pool *pl, const j3d_tune *t)
     }
     pl->variant = v;
     pl->zchunk = zc;
+    pl->tuned = t != nullptr;
     return J3D_OK;
 }
 
@@ -648,19 +645,6 @@ j3d_status j3d_pool_set_two_sweep(j3d_pool *pl, int32_t enable)
     for (const Req &r : pl->reqs)
         if (r.state != R_FREE)
             return set_error(J3D_ESTATE, "sweeps per launch can change only while the pool is empty");
-    if (enable && !pl->host_probs2) {
-        j3d_status st = hip_status(hipHostMalloc((void **)&pl->host_probs2, pl->max_slots * sizeof(ProbDesc), 0),
-                                   "pinned table");
-        if (st != J3D_OK) return st;
-        st = hip_status(hipHostMalloc((void **)&pl->host_tiles2,
-                                      (size_t)pl->max_slots * kPoolTilesPerReq * sizeof(Tile), 0),
-                        "pinned table");
-        if (st != J3D_OK) {
-            (void)hipHostFree(pl->host_probs2);
-            pl->host_probs2 = nullptr;
-            return st;
-        }
-    }
     pl->two_sweep = enable != 0;
     return J3D_OK;
 }
@@ -709,8 +693,6 @@ j3d_status j3d_pool_destroy(j3d_pool *pl)
     if (pl->host_probs) (void)hipHostFree(pl->host_probs);
     if (pl->host_blocks) (void)hipHostFree(pl->host_blocks);
     if (pl->host_tiles) (void)hipHostFree(pl->host_tiles);
-    if (pl->host_probs2) (void)hipHostFree(pl->host_probs2);
-    if (pl->host_tiles2) (void)hipHostFree(pl->host_tiles2);
     delete pl;
     return st;
 }

@@ -58,12 +58,7 @@ j3d_status upload_tables(const Plan &plan, char *arena, hipStream_t stream)
                                   plan.blocks.size() * sizeof(BlockDesc), hipMemcpyHostToDevice, stream);
     if (e != hipSuccess) return hip_status(e, "upload blocks");
     std::vector<ProbDesc> probs(plan.probs.size());
-    for (size_t i = 0; i < probs.size(); ++i) {
-        std::memset(&probs[i], 0, sizeof(ProbDesc));
-        probs[i].res_slot = (int32_t)i;
-        probs[i].limit = plan.probs[i].iters;
-        probs[i].flags = PF_RES_LAST;
-    }
+    for (size_t i = 0; i < probs.size(); ++i) fill_prob(plan, (int32_t)i, 0, &probs[i]);
     e = hipMemcpyAsync(arena + plan.off_probs, probs.data(), probs.size() * sizeof(ProbDesc),
                        hipMemcpyHostToDevice, stream);
     if (e != hipSuccess) return hip_status(e, "upload problems");
@@ -93,6 +88,30 @@ j3d_status upload_tiles(const Plan &plan, const std::vector<Tile> &tiles, char *
                                   hipMemcpyHostToDevice, stream);
     if (e != hipSuccess) return hip_status(e, "upload tiles");
     return hip_status(hipStreamSynchronize(stream), "upload tiles");
+}
+
+j3d_status upload_multi(const Plan &plan, const MultiPlan &m, char *arena, hipStream_t stream)
+{
+    if (m.shape < 0) return J3D_OK;
+    if (m.tiles.size() > plan.mtiles_cap) return set_error(J3D_EINVAL, "tile table overflow");
+    hipError_t e = hipMemcpyAsync(arena + plan.off_mtiles, m.tiles.data(), m.tiles.size() * sizeof(Tile),
+                                  hipMemcpyHostToDevice, stream);
+    if (e != hipSuccess) return hip_status(e, "upload tiles");
+    return hip_status(hipStreamSynchronize(stream), "upload tiles");
+}
+
+MultiArgs multi_args(const Plan &plan, char *arena)
+{
+    MultiArgs a;
+    std::memset(&a, 0, sizeof a);
+    a.base = reinterpret_cast<double *>(arena);
+    a.blocks = reinterpret_cast<const BlockDesc *>(arena + plan.off_blocks);
+    a.probs = reinterpret_cast<const ProbDesc *>(arena + plan.off_probs);
+    a.tiles = reinterpret_cast<const Tile *>(arena + plan.off_mtiles);
+    a.maps = arena;
+    a.end = arena + plan.total;
+    a.res = reinterpret_cast<unsigned long long *>(arena + plan.off_res);
+    return a;
 }
 
 j3d_status init_fields(const Plan &plan, char *arena, hipStream_t stream)
@@ -185,6 +204,8 @@ struct j3d_solver {
     bool ghosts_fresh = false;
     int64_t iters_done = 0;
     j3d_tune tune{0, 0, 0};
+    bool tuned = false;          // shape set by the caller: GRAPH keeps to it
+    MultiPlan multi;             // several sweeps per launch (GRAPH, TWO_SWEEP)
     int zchunk = 1;
     int32_t ntiles = 0;
     std::vector<Tile> tiles;
@@ -565,33 +586,16 @@ j3d_status run_host_staged(j3d_solver *s, int p, bool res, bool overlap, hipStre
     return sweep_tiles(s, p, false, res, 0, s->ntiles, main);
 }
 
-// One launch of the two-sweep kernel: iterate in buffer p -> two sweeps later
-// in buffer p^1.  Whole planes when the x-y tiles alone give every compute
-// unit two workgroups, else z-chunks (at least 4 planes) for about that many.
-j3d_status two_sweep_launch(j3d_solver *s, int p, bool res, hipStream_t st)
+// One multi-sweep launch: `ns` sweeps from buffer p into buffer p^1.
+j3d_status multi_launch(j3d_solver *s, int p, int ns, bool res, hipStream_t st)
 {
-    const BlockDesc &B = s->plan.blocks[0];
-    double *base = reinterpret_cast<double *>(s->arena);
-    TwoStepArgs a;
-    std::memset(&a, 0, sizeof a);
-    a.ex = B.ext[0];
-    a.ey = B.ext[1];
-    a.ez = B.ext[2];
-    a.pitch = B.pitch;
-    a.res = reinterpret_cast<unsigned long long *>(s->arena + s->plan.off_res);
-    int ntx = 0, nty = 0, ntz = 0;
-    twostep_tiles(a.ex, a.ey, a.ez, 0, &ntx, &nty, &ntz);
-    int zc = 0;
-    if (ntx * nty < 2 * s->cus) {
-        const int want = (2 * s->cus + ntx * nty - 1) / (ntx * nty);
-        zc = std::max(4, (a.ez + want - 1) / want);
-    }
-    twostep_tiles(a.ex, a.ey, a.ez, zc, &a.ntx, &a.nty, &a.ntz);
-    a.cur = base + B.off[p];
-    a.nxt = base + B.off[p ^ 1];
-    a.xh = base + B.xoff[p];
-    a.want_res = res ? 1 : 0;
-    return hip_status(launch_twostep(a, st), "two-sweep launch");
+    MultiArgs a = multi_args(s->plan, s->arena);
+    a.tile_count = (int32_t)s->multi.tiles.size();
+    a.parity = p;
+    a.nsweeps = ns;
+    a.flags = res ? MS_RES : 0;
+    const int grid = xcd_split(s->multi.work, 0, a.tile_count, a.xcut);
+    return hip_status(launch_multisweep(s->multi.shape, s->multi.general, a, grid, st), "multi-sweep launch");
 }
 
 // One sweep of `mode` reading parity p, enqueued on st.
@@ -617,8 +621,8 @@ j3d_status one_sweep(j3d_solver *s, int mode, int p, bool res, int slot, hipStre
     case J3D_HOST_OVERLAP:
         // the overlapped update's shell pass carries no residual
         return run_host_staged(s, p, res, !res, st);
-    case J3D_TWO_SWEEP:  // one launch, two sweeps
-        return two_sweep_launch(s, p, res, st);
+    case J3D_TWO_SWEEP:  // one launch, several sweeps
+        return multi_launch(s, p, s->multi.t, res, st);
     }
     return set_error(J3D_EINVAL, "unknown mode %d", mode);
 }
@@ -638,20 +642,18 @@ j3d_status finish_run(j3d_solver *s, double *residual_out, const unsigned long l
     return J3D_OK;
 }
 
-// TWO_SWEEP: iters / 2 two-sweep launches (each reads the current buffer and
-// writes the other), replayed from HIP graphs of 24 launches when captured,
-// then one fused sweep if iters is odd.  The residual comes from the launch
-// that performs the last sweep, which is never inside a graph.
-j3d_status run_two_sweep(j3d_solver *s, int64_t iters, bool want_res, bool captured)
+// Multi-sweep launches of multi.t sweeps each, the last one with what is left;
+// each reads the current buffer and writes the other.  When captured, 24
+// launches are replayed per HIP graph.  The residual comes from the last
+// launch, which is never inside a graph.
+j3d_status run_multi(j3d_solver *s, int64_t iters, bool want_res, bool captured)
 {
     int p = s->parity;
-    const int64_t pairs = iters / 2;
-    const bool res_in_pair = want_res && (iters & 1) == 0;
-    int64_t k = 0;
+    const int t = s->multi.t;
+    int64_t done = 0;
     if (captured) {
-        const int g = graph_sweeps(J3D_TWO_SWEEP);
-        const int64_t plain = pairs - (res_in_pair ? 1 : 0);
-        for (; k + g <= plain; k += g) {
+        const int64_t g = (int64_t)graph_sweeps(J3D_TWO_SWEEP) * t;
+        for (; done + g < iters; done += g) {
             hipGraphExec_t exec = nullptr;
             j3d_status st = get_graph(s, J3D_TWO_SWEEP, p, 0, &exec);
             if (st != J3D_OK) return st;
@@ -659,19 +661,16 @@ j3d_status run_two_sweep(j3d_solver *s, int64_t iters, bool want_res, bool captu
             if (st != J3D_OK) return st;
         }
     }
-    for (; k < pairs; ++k) {
-        j3d_status st = two_sweep_launch(s, p, res_in_pair && k + 1 == pairs, s->stream);
-        if (st != J3D_OK) return st;
-        p ^= 1;
-    }
-    if (iters & 1) {
-        const int slot = persistent_mode(s, J3D_FUSED) ? (int)(s->persist_launches++ & 1) : 0;
-        j3d_status st = one_sweep(s, J3D_FUSED, p, want_res, slot, s->stream);
+    while (done < iters) {
+        const int ns = (int)std::min<int64_t>(t, iters - done);
+        done += ns;
+        j3d_status st = multi_launch(s, p, ns, want_res && done == iters, s->stream);
         if (st != J3D_OK) return st;
         p ^= 1;
     }
     s->parity = p;
     s->iters_done += iters;
+    s->ghosts_fresh = false;
     return J3D_OK;
 }
 
@@ -706,6 +705,10 @@ j3d_status j3d_create(const j3d_problem *p, void *dev_arena, uint64_t arena_byte
         j3d_tune t;
         default_tune(s->plan, s->cus, &t);
         st = apply_tune(s, t);
+    }
+    if (st == J3D_OK) {
+        make_multi(s->plan, nullptr, s->cus, s->plan.mtiles_cap, &s->multi);
+        st = upload_multi(s->plan, s->multi, s->arena, s->stream);
     }
     if (st == J3D_OK)
         st = hip_status(launch_fill_u32(reinterpret_cast<unsigned int *>(s->arena + s->plan.off_queue), 16, 0,
@@ -773,7 +776,9 @@ j3d_status j3d_set_tune(j3d_solver *s, const j3d_tune *t)
     } else {
         default_tune(s->plan, s->cus, &d);
     }
-    return apply_tune(s, d);
+    const j3d_status st = apply_tune(s, d);
+    if (st == J3D_OK) s->tuned = t != nullptr;
+    return st;
 }
 
 j3d_status j3d_get_tune(const j3d_solver *s, j3d_tune *out)
@@ -791,16 +796,19 @@ j3d_status j3d_run(j3d_solver *s, int64_t iters, j3d_mode mode_in, double *resid
     bool captured = (mode & J3D_CAPTURED) != 0;
     mode &= ~(int)J3D_CAPTURED;
     if (mode == J3D_GRAPH) {
+        // the same iterates by the fastest launches: several sweeps each,
+        // unless the caller chose the one-sweep kernel's shape
         mode = J3D_FUSED;
         captured = true;
+        if (s->multi.shape >= 0 && !s->tuned) mode = J3D_TWO_SWEEP;
+    } else if (mode == J3D_TWO_SWEEP && s->plan.blocks.size() != 1) {
+        return set_error(J3D_EINVAL, "the two-sweep mode needs a grid of one block (%zu blocks)",
+                         s->plan.blocks.size());
+    } else if (mode == J3D_TWO_SWEEP && s->multi.shape < 0) {
+        mode = J3D_FUSED;
     }
     if (mode < J3D_UNFUSED_BLOCK || mode > J3D_TWO_SWEEP)
         return set_error(J3D_EINVAL, "unknown mode %d", (int)mode_in);
-    if (mode == J3D_TWO_SWEEP) {
-        if (s->plan.blocks.size() != 1)
-            return set_error(J3D_EINVAL, "the two-sweep mode needs a grid of one block (%zu blocks)",
-                             s->plan.blocks.size());
-    }
     if (iters == 0) {
         if (residual_out) *residual_out = 0.0;
         return J3D_OK;
@@ -813,7 +821,7 @@ j3d_status j3d_run(j3d_solver *s, int64_t iters, j3d_mode mode_in, double *resid
             st = hip_status(launch_fill_u64(res, 1, 0ull, s->stream), "residual reset");
             if (st != J3D_OK) return st;
         }
-        st = run_two_sweep(s, iters, want_res, captured);
+        st = run_multi(s, iters, want_res, captured);
         if (st != J3D_OK) return st;
         return finish_run(s, residual_out, res);
     }
@@ -908,6 +916,8 @@ struct j3d_batch {
     std::vector<int32_t> order;         // problems by iteration count, descending
     std::vector<int32_t> prefix_tiles;  // tiles of the first k problems of `order`
     std::vector<uint64_t> work;         // prefix sums of the tiles' estimated work
+    MultiPlan multi;                    // several sweeps per launch
+    bool tuned = false;                 // j3d_batch_run keeps to the caller's one-sweep shape
     int64_t max_iters = 0;
     bool ran = false;
     uint32_t persist_launches = 0;
@@ -963,6 +973,8 @@ j3d_status j3d_batch_create(int32_t count, const j3d_problem *probs, const int64
     for (int32_t i = 0; i < count; ++i) b->order[i] = i;
     std::stable_sort(b->order.begin(), b->order.end(),
                      [&](int32_t x, int32_t y) { return iters[x] > iters[y]; });
+    b->tuned = tune && !(tune->variant == -1 && tune->zchunk == 0 && tune->blocks_per_cu == 0);
+    make_multi(b->plan, &b->order, cus, b->plan.mtiles_cap, &b->multi);
     std::vector<Tile> tiles;
     b->prefix_tiles.assign(1, 0);
     for (int32_t k = 0; k < count; ++k) {
@@ -974,6 +986,7 @@ j3d_status j3d_batch_create(int32_t count, const j3d_problem *probs, const int64
     tile_work(tiles, &b->work);
     st = upload_tables(b->plan, b->arena, b->stream);
     if (st == J3D_OK) st = upload_tiles(b->plan, tiles, b->arena, b->stream);
+    if (st == J3D_OK) st = upload_multi(b->plan, b->multi, b->arena, b->stream);
     if (st == J3D_OK)
         st = hip_status(launch_fill_u32(reinterpret_cast<unsigned int *>(b->arena + b->plan.off_queue), 16, 0,
                                         b->stream),
@@ -987,15 +1000,15 @@ j3d_status j3d_batch_create(int32_t count, const j3d_problem *probs, const int64
     return J3D_OK;
 }
 
-j3d_status j3d_batch_run(j3d_batch *b, double *residuals_out)
+}  // extern "C"
+
+namespace {
+
+// One launch per sweep, covering every tile of every problem with sweeps left.
+j3d_status batch_one_sweep(j3d_batch *b, unsigned long long *res)
 {
-    if (!b) return set_error(J3D_EINVAL, "batch is NULL");
-    if (b->ran) return set_error(J3D_ESTATE, "batch already ran");
     const int32_t count = (int32_t)b->plan.probs.size();
-    unsigned long long *res = reinterpret_cast<unsigned long long *>(b->arena + b->plan.off_res);
     j3d_status st = refresh_halos(b->plan, b->arena, 0, (int32_t)b->plan.blocks.size(), 0, b->stream);
-    if (st != J3D_OK) return st;
-    st = hip_status(launch_fill_u64(res, count, 0ull, b->stream), "residual reset");
     if (st != J3D_OK) return st;
     SweepArgs a;
     std::memset(&a, 0, sizeof a);
@@ -1024,9 +1037,43 @@ j3d_status j3d_batch_run(j3d_batch *b, double *residuals_out)
         st = hip_status(launch_sweep(b->tune.variant, a, grid, b->stream), "batch sweep launch");
         if (st != J3D_OK) return st;
     }
-    b->ran = true;
-    b->final_parity.resize(count);
     for (int32_t i = 0; i < count; ++i) b->final_parity[i] = (int)(b->plan.probs[i].iters & 1);
+    return J3D_OK;
+}
+
+// multi.t sweeps per launch: launch k covers the problems with more than
+// k * multi.t sweeps; a problem's last launch takes what is left of its count.
+j3d_status batch_multi_sweep(j3d_batch *b)
+{
+    const int32_t count = (int32_t)b->plan.probs.size();
+    const int t = b->multi.t;
+    MultiArgs a = multi_args(b->plan, b->arena);
+    a.flags = MS_MULTI;
+    int32_t active = count;
+    for (int64_t k = 0; k * t < b->max_iters; ++k) {
+        while (active > 0 && b->plan.probs[b->order[active - 1]].iters <= k * t) --active;
+        a.step = k;
+        a.tile_count = b->multi.prefix[active];
+        const int grid = xcd_split(b->multi.work, 0, a.tile_count, a.xcut);
+        j3d_status st = hip_status(launch_multisweep(b->multi.shape, b->multi.general, a, grid, b->stream),
+                                   "multi-sweep batch launch");
+        if (st != J3D_OK) return st;
+    }
+    for (int32_t i = 0; i < count; ++i)
+        b->final_parity[i] = (int)((b->plan.probs[i].iters + t - 1) / t & 1);
+    return J3D_OK;
+}
+
+j3d_status batch_run(j3d_batch *b, bool multi, double *residuals_out)
+{
+    const int32_t count = (int32_t)b->plan.probs.size();
+    unsigned long long *res = reinterpret_cast<unsigned long long *>(b->arena + b->plan.off_res);
+    j3d_status st = hip_status(launch_fill_u64(res, count, 0ull, b->stream), "residual reset");
+    if (st != J3D_OK) return st;
+    b->final_parity.resize(count);
+    st = multi ? batch_multi_sweep(b) : batch_one_sweep(b, res);
+    if (st != J3D_OK) return st;
+    b->ran = true;
     if (residuals_out) {
         std::vector<unsigned long long> bits(count);
         st = hip_status(hipMemcpyAsync(bits.data(), res, count * sizeof(unsigned long long),
@@ -1039,125 +1086,26 @@ j3d_status j3d_batch_run(j3d_batch *b, double *residuals_out)
     return J3D_OK;
 }
 
+}  // namespace
+
+extern "C" {
+
+j3d_status j3d_batch_run(j3d_batch *b, double *residuals_out)
+{
+    if (!b) return set_error(J3D_EINVAL, "batch is NULL");
+    if (b->ran) return set_error(J3D_ESTATE, "batch already ran");
+    return batch_run(b, b->multi.shape >= 0 && !b->tuned, residuals_out);
+}
+
 j3d_status j3d_batch_run_two_sweep(j3d_batch *b, double *residuals_out)
 {
     if (!b) return set_error(J3D_EINVAL, "batch is NULL");
     if (b->ran) return set_error(J3D_ESTATE, "batch already ran");
-    const int32_t count = (int32_t)b->plan.probs.size();
-    for (int32_t i = 0; i < count; ++i)
+    for (size_t i = 0; i < b->plan.probs.size(); ++i)
         if (b->plan.probs[i].nblocks != 1)
-            return set_error(J3D_EINVAL, "two sweeps per launch need undivided problems (problem %d has %d blocks)",
+            return set_error(J3D_EINVAL, "two sweeps per launch need undivided problems (problem %zu has %d blocks)",
                              i, b->plan.probs[i].nblocks);
-    // two-sweep tiles: problems by pair count, longest first, so the tiles
-    // active at pair step s are a prefix of the table
-    constexpr int kZchunk = 64;  // measured: 32 and 128 were 3% and 5% slower on the batched workload
-    std::vector<int32_t> order(count);
-    for (int32_t i = 0; i < count; ++i) order[i] = i;
-    std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) {
-        return b->plan.probs[x].iters / 2 > b->plan.probs[y].iters / 2;
-    });
-    std::vector<Tile> tiles2;
-    std::vector<int32_t> prefix2(1, 0);
-    for (int32_t k = 0; k < count; ++k) {
-        const ProbPlan &pp = b->plan.probs[order[k]];
-        twostep_make_tiles(b->plan.blocks.data(), pp.block_begin, pp.block_begin + 1, kZchunk, &tiles2);
-        prefix2.push_back((int32_t)tiles2.size());
-    }
-    if (tiles2.size() > b->plan.tiles_cap)
-        return set_error(J3D_EINVAL, "two-sweep tiles (%zu) exceed the tile table (%llu)", tiles2.size(),
-                         (unsigned long long)b->plan.tiles_cap);
-
-    unsigned long long *res = reinterpret_cast<unsigned long long *>(b->arena + b->plan.off_res);
-    ProbDesc *probs_dev = reinterpret_cast<ProbDesc *>(b->arena + b->plan.off_probs);
-    j3d_status st = hip_status(launch_fill_u64(res, count, 0ull, b->stream), "residual reset");
-    if (st != J3D_OK) return st;
-    auto upload_probs = [&](const std::vector<ProbDesc> &pd) {
-        j3d_status r = hip_status(hipMemcpyAsync(probs_dev, pd.data(), pd.size() * sizeof(ProbDesc),
-                                                 hipMemcpyHostToDevice, b->stream),
-                                  "problem table");
-        return r == J3D_OK ? hip_status(hipStreamSynchronize(b->stream), "problem table") : r;
-    };
-    std::vector<ProbDesc> pd(count);
-    // an odd count starts with one ordinary sweep (residual only if it is the last)
-    bool any_odd = false;
-    for (int32_t i = 0; i < count; ++i) {
-        std::memset(&pd[i], 0, sizeof(ProbDesc));
-        const int64_t it = b->plan.probs[i].iters;
-        pd[i].limit = it & 1;
-        pd[i].res_slot = i;
-        pd[i].flags = it == 1 ? PF_RES_LAST : 0;
-        any_odd = any_odd || (it & 1);
-    }
-    if (any_odd) {
-        st = upload_probs(pd);
-        if (st != J3D_OK) return st;
-        SweepArgs a;
-        std::memset(&a, 0, sizeof a);
-        a.base = reinterpret_cast<double *>(b->arena);
-        a.blocks = reinterpret_cast<const BlockDesc *>(b->arena + b->plan.off_blocks);
-        a.probs = probs_dev;
-        a.tiles = reinterpret_cast<const Tile *>(b->arena + b->plan.off_tiles);
-        a.res = res;
-        a.queue = reinterpret_cast<unsigned int *>(b->arena + b->plan.off_queue);
-        a.zchunk = b->zchunk;
-        a.step = 0;
-        a.tile_count = b->prefix_tiles[count];
-        a.flags = SW_FUSED | SW_MULTI;
-        int grid;
-        if (b->tune.blocks_per_cu > 0) {
-            a.flags |= SW_PERSIST;
-            a.queue_slot = (int)(b->persist_launches++ & 1);
-            grid = std::min(a.tile_count, b->cus * b->tune.blocks_per_cu);
-        } else {
-            grid = xcd_split(b->work, 0, a.tile_count, a.xcut);
-        }
-        st = hip_status(launch_sweep(b->tune.variant, a, grid, b->stream), "batch sweep launch");
-        if (st != J3D_OK) return st;
-    }
-    // then iters / 2 two-sweep launches per problem
-    for (int32_t i = 0; i < count; ++i) {
-        const int64_t it = b->plan.probs[i].iters;
-        pd[i].base = it & 1;
-        pd[i].limit = it / 2;
-        pd[i].flags = 0;
-    }
-    st = upload_probs(pd);
-    if (st == J3D_OK) st = upload_tiles(b->plan, tiles2, b->arena, b->stream);
-    if (st != J3D_OK) return st;
-    TwoStepArgs a2;
-    std::memset(&a2, 0, sizeof a2);
-    a2.base = reinterpret_cast<double *>(b->arena);
-    a2.blocks = reinterpret_cast<const BlockDesc *>(b->arena + b->plan.off_blocks);
-    a2.probs = probs_dev;
-    a2.tiles = reinterpret_cast<const Tile *>(b->arena + b->plan.off_tiles);
-    a2.res = res;
-    a2.zchunk = kZchunk;
-    int32_t active = count;
-    const int64_t max_pairs = count > 0 ? b->plan.probs[order[0]].iters / 2 : 0;
-    for (int64_t s2 = 0; s2 < max_pairs; ++s2) {
-        while (active > 0 && b->plan.probs[order[active - 1]].iters / 2 <= s2) --active;
-        a2.step = s2;
-        a2.tile_begin = 0;
-        a2.tile_count = prefix2[active];
-        st = hip_status(launch_twostep(a2, b->stream), "two-sweep batch launch");
-        if (st != J3D_OK) return st;
-    }
-    b->ran = true;
-    b->final_parity.resize(count);
-    for (int32_t i = 0; i < count; ++i) {
-        const int64_t it = b->plan.probs[i].iters;
-        b->final_parity[i] = (int)(((it & 1) + it / 2) & 1);
-    }
-    if (residuals_out) {
-        std::vector<unsigned long long> bits(count);
-        st = hip_status(hipMemcpyAsync(bits.data(), res, count * sizeof(unsigned long long),
-                                       hipMemcpyDeviceToHost, b->stream),
-                        "residual readback");
-        if (st == J3D_OK) st = hip_status(hipStreamSynchronize(b->stream), "residual readback");
-        if (st != J3D_OK) return st;
-        for (int32_t i = 0; i < count; ++i) std::memcpy(&residuals_out[i], &bits[i], sizeof(double));
-    }
-    return J3D_OK;
+    return batch_run(b, b->multi.shape >= 0, residuals_out);
 }
 
 j3d_status j3d_batch_get_interior(j3d_batch *b, int32_t i, double *dst, int dst_on_device)

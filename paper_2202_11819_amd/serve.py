@@ -229,7 +229,8 @@ def batch_bench(tune=None, retune=False, batch_only=False, two_sweep=False, loop
         tune, searched = tune_batch(problems, iters, log=log, force=retune, report=True)
         search = {"candidates": searched, "seconds": round(time.perf_counter() - t0, 2)}
     tune = tuple(tune)
-    log(f"[batch] tune {tune} ({j3d.variants()[tune[0]]})")
+    tile = list(j3d.variants()[tune[0]]) if tune[0] >= 0 else None  # None: several sweeps per launch
+    log(f"[batch] tune {tune} ({tile})")
 
     def timed_batch(t, two=False):
         b = Batch(problems, iters, tune=t)
@@ -246,7 +247,7 @@ def batch_bench(tune=None, retune=False, batch_only=False, two_sweep=False, loop
     tb = min(timed_batch(tune) for _ in range(2))
     out = {"metric": "batched FP64 Jacobi3D GLUP/s (256 problems, one launch per sweep)",
            "value": round(lups / tb / 1e9, 2), "unit": "GLUP/s", "higher_is_better": True,
-           "batched_s": round(tb, 4), "tune": list(tune), "tile": list(j3d.variants()[tune[0]]),
+           "batched_s": round(tb, 4), "tune": list(tune), "tile": tile,
            "autotune": search,
            "config": {"workload": f"256 independent problems, per-axis size log-uniform in [32, 256], "
                                   f"per-face bc U[-1,1], 100..1000 sweeps, {lups / 1e9:.1f} GLUP in total",
