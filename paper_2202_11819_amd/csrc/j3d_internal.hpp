@@ -241,14 +241,14 @@ int launch_exchange(double *base, const BlockDesc *blocks, int32_t block_begin, 
 // Unpack R[b][f] into the halo storage of parity `parity`.
 int launch_unpack(double *base, const BlockDesc *blocks, int32_t block_begin, int32_t nblocks,
                   int32_t max_face, int parity, int face_mask, void *stream);
-// Dense global array chunk (planes z0..z1-1) <-> block interiors of parity p.
-// maps: for axis a, n[a] pairs (block coordinate, local coordinate).
-int launch_scatter(double *base, const BlockDesc *blocks, int32_t block_base, const int32_t nb[3],
-                   const int32_t *maps, const int64_t n[3], int64_t z0, int64_t z1,
-                   const double *src, int parity, void *stream);
-int launch_gather(const double *base, const BlockDesc *blocks, int32_t block_base,
-                  const int32_t nb[3], const int32_t *maps, const int64_t n[3], int64_t z0,
-                  int64_t z1, double *dst, int parity, void *stream);
+// Dense global array chunk (planes z0..z1-1 of an n[0] x n[1] x ... grid) <->
+// block interiors of parity p.
+struct DenseShape {
+    int32_t max_plane, max_depth;  // largest x-y plane (cells) and depth of the blocks
+    bool even_rows;                // every block is an even number of cells wide
+};
+int launch_dense(double *base, const BlockDesc *blocks, int32_t block_begin, int32_t nblocks, const DenseShape &d,
+                 const int64_t n[2], int64_t z0, int64_t z1, double *dense, int parity, bool to_dense, void *stream);
 // Per-cell Dirichlet face f from a dense device array into both parities.
 int launch_set_face(double *base, const BlockDesc *blocks, int32_t block_base, const int32_t nb[3],
                     const int32_t *maps, const int64_t n[3], int face, const double *src,
@@ -256,8 +256,4 @@ int launch_set_face(double *base, const BlockDesc *blocks, int32_t block_base, c
 int launch_fill_u64(unsigned long long *p, int64_t count, unsigned long long value, void *stream);
 int launch_fill_u32(unsigned int *p, int64_t count, unsigned int value, void *stream);
 int launch_copy(void *dst, const void *src, uint64_t bytes, void *stream);
-// Dense interior of one single-block problem gathered into `dst` (device).
-int launch_gather_block(const double *base, const BlockDesc *blocks, int32_t block, int parity,
-                        double *dst, void *stream);
-
 }  // namespace j3d

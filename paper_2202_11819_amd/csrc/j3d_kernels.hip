@@ -866,40 +866,61 @@ struct DenseMap {
     int32_t nb0, nb1, nb2;
 };
 
-// Arena offset (in doubles) of global interior cell (i, j, k) in parity `parity`.
-__device__ __forceinline__ int64_t dense_to_block(const BlockDesc *blocks, int block_base,
-                                                  const DenseMap &m, int64_t i, int64_t j,
-                                                  int64_t k, int parity)
+// Dense grid array <-> block interiors (planes z0 .. z1-1 of the grid).  A
+// workgroup copies runs of one block: rows are unpadded, so a block plane is
+// contiguous in the field, and only the dense side needs the cell's row, one
+// FP64 multiplication per cell ((e + 0.5) / d is at least 0.5 / d away from an
+// integer and e < 2^31, so the rounded product has the right floor).  Bound by
+// HBM; the earlier form found every cell from its dense index by three 64-bit
+// divisions and two table lookups.  512^3 as 8^3 blocks: out 726 -> 344 us, in
+// 685 -> 352 us (6.1 TB/s, the streaming copy's rate).
+// V: cells per access, 2 where every row starts on 16 bytes on both sides.
+// FLAT: runs over the whole block instead of one plane each, for blocks whose
+// planes would leave most of a workgroup idle (96^3 as 12^3 blocks: 8.7
+// against 19 us by planes).
+template <int V, bool OUT, bool FLAT>
+__global__ __launch_bounds__(256) void dense_kernel(double *base, const BlockDesc *blocks, int block_begin, int nblocks,
+                                                    int64_t n0, int64_t n1, int z0, int z1, double *dense, int parity)
 {
-    const int bx = m.mx[2 * i], lx = m.mx[2 * i + 1];
-    const int by = m.my[2 * j], ly = m.my[2 * j + 1];
-    const int bz = m.mz[2 * k], lz = m.mz[2 * k + 1];
-    const BlockDesc &B = blocks[block_base + bx + m.nb0 * (by + m.nb1 * bz)];
-    const int pitch = B.pitch, ey = B.ext[1];
-    return B.off[parity] + (int64_t)(lz + 1) * plane_stride(pitch, ey) + (int64_t)(ly + 1) * pitch + lx;
-}
-
-__global__ __launch_bounds__(256) void scatter_kernel(double *base, const BlockDesc *blocks,
-                                                      int block_base, DenseMap m, int64_t n0,
-                                                      int64_t n1, int64_t z0, int64_t count,
-                                                      const double *src, int parity)
-{
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < count; g += stride) {
-        const int64_t i = g % n0, j = (g / n0) % n1, k = z0 + g / (n0 * n1);
-        base[dense_to_block(blocks, block_base, m, i, j, k, parity)] = src[g];
-    }
-}
-
-__global__ __launch_bounds__(256) void gather_kernel(const double *base, const BlockDesc *blocks,
-                                                     int block_base, DenseMap m, int64_t n0,
-                                                     int64_t n1, int64_t z0, int64_t count,
-                                                     double *dst, int parity)
-{
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < count; g += stride) {
-        const int64_t i = g % n0, j = (g / n0) % n1, k = z0 + g / (n0 * n1);
-        dst[g] = base[dense_to_block(blocks, block_base, m, i, j, k, parity)];
+    typedef double vec __attribute__((ext_vector_type(V)));
+    constexpr int kRun = 4;  // accesses per thread in flight
+    for (int b = blockIdx.z; b < nblocks; b += gridDim.z) {
+        const BlockDesc &B = blocks[block_begin + b];
+        const int ex = B.ext[0], plane = ex * B.ext[1];
+        const int first = max(0, z0 - B.org[2]), last = min(B.ext[2], z1 - B.org[2]);
+        const double inv = 1.0 / ex, invp = 1.0 / plane;
+        const int64_t ps = plane_stride(B.pitch, B.ext[1]);
+        for (int z = first + (int)blockIdx.y; z < last; z += FLAT ? last : (int)gridDim.y) {
+            double *F = base + B.off[parity] + (z + 1) * ps + B.pitch;
+            double *D = dense + ((int64_t)(B.org[2] + z - z0) * n1 + B.org[1]) * n0 + B.org[0];
+            const int64_t cells = FLAT ? (int64_t)plane * (last - first) : plane;
+            for (int64_t e0 = (int64_t)blockIdx.x * (256 * kRun * V); e0 < cells;
+                 e0 += (int64_t)gridDim.x * (256 * kRun * V)) {
+                vec v[kRun];
+                double *to[kRun];
+#pragma unroll
+                for (int u = 0; u < kRun; ++u) {
+                    const int64_t i = e0 + (threadIdx.x + 256 * u) * V;
+                    int e = (int)(i < cells ? i : 0);
+                    double *f = F, *d = D;
+                    if (FLAT) {
+                        const int q = (int)(((double)e + 0.5) * invp);
+                        e -= q * plane;
+                        f += q * ps;
+                        d += q * n1 * n0;
+                    }
+                    const int y = (int)(((double)e + 0.5) * inv);
+                    f += e;
+                    d += (int64_t)y * n0 + (e - y * ex);
+                    to[u] = OUT ? d : f;
+                    v[u] = __builtin_nontemporal_load(reinterpret_cast<const vec *>(OUT ? f : d));
+                }
+#pragma unroll
+                for (int u = 0; u < kRun; ++u)
+                    if (e0 + (threadIdx.x + 256 * u) * V < cells)
+                        __builtin_nontemporal_store(v[u], reinterpret_cast<vec *>(to[u]));
+            }
+        }
     }
 }
 
@@ -948,22 +969,6 @@ __global__ __launch_bounds__(256) void set_face_kernel(double *base, const Block
                 base[B.off[q] + (face == 4 ? 0 : (int64_t)(ez + 1)) * PS + (int64_t)(ly + 1) * pitch + lx] = v;
             }
         }
-    }
-}
-
-__global__ __launch_bounds__(256) void gather_block_kernel(const double *base,
-                                                           const BlockDesc *blocks, int block,
-                                                           int parity, double *dst)
-{
-    const BlockDesc &B = blocks[block];
-    const int ex = B.ext[0], ey = B.ext[1], ez = B.ext[2];
-    const int64_t count = (int64_t)ex * ey * ez;
-    const int64_t PS = plane_stride(B.pitch, ey);
-    const double *F = base + B.off[parity];
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < count; g += stride) {
-        const int64_t x = g % ex, y = (g / ex) % ey, z = g / ((int64_t)ex * ey);
-        dst[g] = F[(z + 1) * PS + (y + 1) * B.pitch + x];
     }
 }
 
@@ -1153,27 +1158,25 @@ int launch_shell(double *base, const BlockDesc *blocks, int32_t block_begin, int
     return (int)hipGetLastError();
 }
 
-int launch_scatter(double *base, const BlockDesc *blocks, int32_t block_base, const int32_t nb[3],
-                   const int32_t *maps, const int64_t n[3], int64_t z0, int64_t z1,
-                   const double *src, int parity, void *stream)
+int launch_dense(double *base, const BlockDesc *blocks, int32_t block_begin, int32_t nblocks, const DenseShape &d,
+                 const int64_t n[2], int64_t z0, int64_t z1, double *dense, int parity, bool to_dense, void *stream)
 {
-    const DenseMap m{maps, maps + 2 * n[0], maps + 2 * (n[0] + n[1]), nb[0], nb[1], nb[2]};
-    const int64_t count = n[0] * n[1] * (z1 - z0);
-    hipLaunchKernelGGL(scatter_kernel, dim3(grid_for(count, 256, 65536)), dim3(256), 0,
-                       (hipStream_t)stream, base, blocks, block_base, m, n[0], n[1], z0, count,
-                       src, parity);
-    return (int)hipGetLastError();
-}
-
-int launch_gather(const double *base, const BlockDesc *blocks, int32_t block_base,
-                  const int32_t nb[3], const int32_t *maps, const int64_t n[3], int64_t z0,
-                  int64_t z1, double *dst, int parity, void *stream)
-{
-    const DenseMap m{maps, maps + 2 * n[0], maps + 2 * (n[0] + n[1]), nb[0], nb[1], nb[2]};
-    const int64_t count = n[0] * n[1] * (z1 - z0);
-    hipLaunchKernelGGL(gather_kernel, dim3(grid_for(count, 256, 65536)), dim3(256), 0,
-                       (hipStream_t)stream, base, blocks, block_base, m, n[0], n[1], z0, count,
-                       dst, parity);
+    const bool pairs = d.even_rows && n[0] % 2 == 0 && reinterpret_cast<uintptr_t>(dense) % 16 == 0;
+    const int per = 1024 * (pairs ? 2 : 1);  // cells of one workgroup's run
+    const int64_t depth = d.max_depth < z1 - z0 ? d.max_depth : z1 - z0;
+    // planes below half a run are copied block by block (block cells < 2^31)
+    const bool flat = d.max_plane < per / 2;
+    const dim3 grid(grid_for(flat ? d.max_plane * depth : d.max_plane, per, 1 << 20),
+                    flat ? 1 : (unsigned)(depth < kMaxGridY ? depth : kMaxGridY),
+                    nblocks < kMaxGridY ? nblocks : kMaxGridY);
+    typedef void (*Fn)(double *, const BlockDesc *, int, int, int64_t, int64_t, int, int, double *, int);
+    static constexpr Fn kFns[8] = {dense_kernel<1, false, false>, dense_kernel<1, false, true>,
+                                   dense_kernel<1, true, false>,  dense_kernel<1, true, true>,
+                                   dense_kernel<2, false, false>, dense_kernel<2, false, true>,
+                                   dense_kernel<2, true, false>,  dense_kernel<2, true, true>};
+    const Fn fn = kFns[(pairs ? 4 : 0) + (to_dense ? 2 : 0) + (flat ? 1 : 0)];
+    hipLaunchKernelGGL(fn, grid, dim3(256), 0, (hipStream_t)stream, base, blocks, block_begin, nblocks, n[0], n[1],
+                       (int)z0, (int)z1, dense, parity);
     return (int)hipGetLastError();
 }
 
@@ -1187,14 +1190,6 @@ int launch_set_face(double *base, const BlockDesc *blocks, int32_t block_base, c
     hipLaunchKernelGGL(set_face_kernel, dim3(grid_for(count, 256, 65536)), dim3(256), 0,
                        (hipStream_t)stream, base, blocks, block_base, m, n[0], n[1], n[2], face,
                        src);
-    return (int)hipGetLastError();
-}
-
-int launch_gather_block(const double *base, const BlockDesc *blocks, int32_t block, int parity,
-                        double *dst, void *stream)
-{
-    hipLaunchKernelGGL(gather_block_kernel, dim3(4096), dim3(256), 0, (hipStream_t)stream, base,
-                       blocks, block, parity, dst);
     return (int)hipGetLastError();
 }
 

@@ -182,9 +182,9 @@ j3d_status start_copy(j3d_pool *pl, int32_t slot)
     const int p = r.buf;
     double *dst = reinterpret_cast<double *>(pl->arena) + r.blk.off[p ^ 1];
     j3d_status st = hip_status(
-        launch_gather_block(reinterpret_cast<double *>(pl->arena),
-                            reinterpret_cast<const BlockDesc *>(pl->arena + pl->lay.off_blocks), slot, p, dst,
-                            pl->stream),
+        launch_dense(reinterpret_cast<double *>(pl->arena),
+                     reinterpret_cast<const BlockDesc *>(pl->arena + pl->lay.off_blocks), slot, 1,
+                     dense_shape(&r.blk, 1), r.n, 0, r.n[2], dst, p, true, pl->stream),
         "result gather");
     if (st != J3D_OK) return st;
     st = hip_status(hipEventRecord(r.gather_ev, pl->stream), "gather event");

@@ -156,35 +156,29 @@ j3d_status copy_dense(const Plan &plan, char *arena, int32_t i, int parity, doub
                       int dense_on_device, bool to_dense, hipStream_t stream)
 {
     const ProbPlan &pp = plan.probs[i];
-    const int32_t *maps = reinterpret_cast<const int32_t *>(arena + pp.maps_off);
     const int64_t *n = pp.d.n;
     const int64_t plane = n[0] * n[1];
-    if (dense_on_device) {
-        const int e = to_dense ? launch_gather(dbase(arena), dblocks(plan, arena), pp.block_begin, pp.d.nb,
-                                               maps, n, 0, n[2], dense, parity, stream)
-                               : launch_scatter(dbase(arena), dblocks(plan, arena), pp.block_begin,
-                                                pp.d.nb, maps, n, 0, n[2], dense, parity, stream);
-        return hip_status(e, to_dense ? "gather launch" : "scatter launch");
-    }
+    const DenseShape shape = dense_shape(plan.blocks.data() + pp.block_begin, (size_t)pp.nblocks);
+    auto copy = [&](int64_t z0, int64_t z1, double *at) {
+        return hip_status(launch_dense(dbase(arena), dblocks(plan, arena), pp.block_begin, pp.nblocks, shape, n, z0, z1,
+                                       at, parity, to_dense, stream),
+                          to_dense ? "gather launch" : "scatter launch");
+    };
+    if (dense_on_device) return copy(0, n[2], dense);
     double *bounce = reinterpret_cast<double *>(arena + plan.off_bounce);
     const int64_t per = std::max<int64_t>(1, (int64_t)plan.bounce_doubles / plane);
     for (int64_t z0 = 0; z0 < n[2]; z0 += per) {
         const int64_t z1 = std::min(n[2], z0 + per);
         const size_t bytes = (size_t)((z1 - z0) * plane) * sizeof(double);
-        hipError_t e;
-        if (to_dense) {
-            j3d_status st = hip_status(launch_gather(dbase(arena), dblocks(plan, arena), pp.block_begin,
-                                                     pp.d.nb, maps, n, z0, z1, bounce, parity, stream),
-                                       "gather launch");
-            if (st != J3D_OK) return st;
-            e = hipMemcpyAsync(dense + z0 * plane, bounce, bytes, hipMemcpyDeviceToHost, stream);
-        } else {
-            e = hipMemcpyAsync(bounce, dense + z0 * plane, bytes, hipMemcpyHostToDevice, stream);
-            if (e == hipSuccess)
-                e = (hipError_t)launch_scatter(dbase(arena), dblocks(plan, arena), pp.block_begin, pp.d.nb,
-                                               maps, n, z0, z1, bounce, parity, stream);
-        }
-        if (e != hipSuccess) return hip_status(e, "dense copy");
+        j3d_status st = J3D_OK;
+        if (!to_dense)
+            st = hip_status(hipMemcpyAsync(bounce, dense + z0 * plane, bytes, hipMemcpyHostToDevice, stream),
+                            "dense copy");
+        if (st == J3D_OK) st = copy(z0, z1, bounce);
+        if (st == J3D_OK && to_dense)
+            st = hip_status(hipMemcpyAsync(dense + z0 * plane, bounce, bytes, hipMemcpyDeviceToHost, stream),
+                            "dense copy");
+        if (st != J3D_OK) return st;
     }
     return hip_status(hipStreamSynchronize(stream), "dense copy");
 }

@@ -124,3 +124,29 @@ def test_noalloc_counts_and_decompositions(env):
                                   torch.cuda.current_stream().cuda_stream)
         want, want_r, _ = oracle.jacobi(n, iters, bc=BC, seed=7, nthreads=NTH)
         assert np.array_equal(out.cpu().numpy(), want) and r == want_r, (n, nblk)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n, nblk, split", [
+    ((64, 32, 6), (1, 1, 1), None), ((63, 33, 5), (1, 1, 1), None),       # one run, and one cell past it
+    ((128, 64, 40), (4, 2, 5), None), ((126, 22, 9), (3, 2, 3), None),    # pairs; planes below half a run
+    ((30, 28, 20), (3, 4, 2), ([9, 11, 10], [7, 7, 7, 7], [1, 19])),      # odd rows inside an even grid
+    ((5, 4, 3), (5, 4, 3), None), ((1, 1, 1), (1, 1, 1), None), ((2, 2100, 3), (1, 1, 1), None)])
+def test_interior_copies_both_ways(env, n, nblk, split):
+    # device arrays on 16 bytes and 8 bytes past them, host arrays
+    import torch
+    _, api, j3d = env
+    count = n[0] * n[1] * n[2]
+    u = torch.rand(count + 1, dtype=torch.float64, device="cuda")
+    with api.Solver(n, nblk=nblk, split=split) as s:
+        for at in (0, 1):
+            src = u[at:at + count]
+            out = torch.full((count + 1,), -1.0, dtype=torch.float64, device="cuda")
+            j3d.j3d_set_interior(s.h, src.data_ptr(), True)
+            j3d.j3d_get_interior(s.h, out[1 - at:].data_ptr(), True)
+            torch.cuda.synchronize()
+            assert torch.equal(out[1 - at:1 - at + count], src)
+            assert out[0 if at == 0 else count] == -1.0  # nothing written past either end
+            assert np.array_equal(s.get_interior().ravel(), src.cpu().numpy())
+            s.set_interior(src.cpu().numpy()[::-1])
+            assert np.array_equal(s.get_interior().ravel(), src.cpu().numpy()[::-1])
