@@ -332,17 +332,18 @@ namespace {
 
 // z pieces of a problem: near-equal, at most zc planes.  With unequal blocks
 // (general) each lies in one block row, and the rows are at least t deep, so a
-// tile reads its own row and its two neighbours at most.
-bool cut_z(const ProbPlan &pp, bool general, int t, int zc, std::vector<Piece> *out)
+// tile reads its own row and its two neighbours at most.  Calls
+// piece(start, planes) for each; false if a row is too shallow.
+template <class F>
+bool cut_z(const ProbPlan &pp, bool general, int t, int zc, F piece)
 {
-    out->clear();
     const bool rows = general && pp.nblocks > 1;
     for (int32_t b = 0; b < (rows ? pp.d.nb[2] : 1); ++b) {
         const int64_t at = rows ? pp.d.org[2][b] : 0, len = rows ? pp.d.ext[2][b] : pp.d.n[2];
         if (rows && len < t) return false;
         const int64_t n = ceil_div(len, zc);
         for (int64_t i = 0; i < n; ++i)
-            out->push_back({(int32_t)(at + i * len / n), (int32_t)((i + 1) * len / n - i * len / n)});
+            piece((int32_t)(at + i * len / n), (int32_t)((i + 1) * len / n - i * len / n));
     }
     return true;
 }
@@ -358,7 +359,6 @@ void make_multi(const Plan &plan, const std::vector<int32_t> *order, int cus, ui
     const int32_t count = (int32_t)(order ? order->size() : plan.probs.size());
     auto prob = [&](int32_t k) -> const ProbPlan & { return plan.probs[order ? (*order)[k] : k]; };
     int64_t depth = 1;
-    double cells = 0;
     bool ragged = false;
     for (int32_t k = 0; k < count; ++k) {
         const ProbPlan &pp = prob(k);
@@ -367,14 +367,13 @@ void make_multi(const Plan &plan, const std::vector<int32_t> *order, int cus, ui
             for (int a = 0; a < 3; ++a) m->general = m->general || plan.blocks[b].ext[a] != A.ext[a];
         depth = std::max(depth, pp.d.n[2]);
         ragged = ragged || x_align(pp) == 1;
-        cells += (double)pp.d.n[0] * pp.d.n[1] * pp.d.n[2];
     }
-    std::vector<Piece> px, py, pz;
+    std::vector<Piece> px, py;
+    std::vector<int64_t> xy(count);
     int best_shape = -1, best_zc = 0;
     double best = 0;
     for (int s = 0; s < mshape_count(); ++s) {
         const MShapeInfo mi = mshape_info(s);
-        std::vector<int64_t> xy(count);
         bool ok = true;
         for (int32_t k = 0; k < count && ok; ++k) {
             const ProbPlan &pp = prob(k);
@@ -384,18 +383,25 @@ void make_multi(const Plan &plan, const std::vector<int32_t> *order, int cus, ui
             ok = multi_span_ok(plan, pp, px, py, mi.t);
         }
         int last_zc = 0;
-        for (int64_t nc = 1; ok && nc <= ceil_div(depth, kMinMultiZ); nc += 1 + nc / 16) {
+        for (int64_t nc = 1; ok && nc <= ceil_div(depth, kMinMultiZ); nc += 1 + nc / 8) {
             const int zc = (int)ceil_div(depth, nc);
             if (zc == last_zc) continue;
             last_zc = zc;
-            double tiles = 0, steps = 0;
+            // the first k + 1 problems run together for as many sweeps as problem k
+            // has more than problem k + 1 (a batch, longest first; else all equal)
+            double tiles = 0, steps = 0, cells = 0, cost = 0;
             for (int32_t k = 0; k < count && ok; ++k) {
-                ok = cut_z(prob(k), m->general, mi.t, zc, &pz);
-                tiles += (double)xy[k] * pz.size();
-                for (const Piece &z : pz) steps += (double)xy[k] * multi_steps(mi, z.len);
+                const ProbPlan &pp = prob(k);
+                ok = cut_z(pp, m->general, mi.t, zc, [&](int32_t, int32_t len) {
+                    tiles += (double)xy[k];
+                    steps += (double)xy[k] * multi_steps(mi, len);
+                });
+                cells += (double)pp.d.n[0] * pp.d.n[1] * pp.d.n[2];
+                const double sweeps = k + 1 < count ? (double)(pp.iters - prob(k + 1).iters)
+                                                    : std::max<double>(1, (double)pp.iters);
+                if (sweeps > 0) cost += sweeps * multi_cost(mi, cus, tiles, steps / tiles, cells, ragged);
             }
             if (!ok || tiles > (double)cap) break;
-            const double cost = multi_cost(mi, cus, tiles, steps / tiles, cells, ragged);
             if (best_shape < 0 || cost < best) {
                 best = cost;
                 best_shape = s;
@@ -409,8 +415,7 @@ void make_multi(const Plan &plan, const std::vector<int32_t> *order, int cus, ui
         const ProbPlan &pp = prob(k);
         cut_axis((int32_t)pp.d.n[0], 64, mi.t, x_align(pp), &px);
         cut_axis((int32_t)pp.d.n[1], mi.rows, mi.t, 1, &py);
-        cut_z(pp, m->general, mi.t, best_zc, &pz);
-        for (const Piece &z : pz)
+        cut_z(pp, m->general, mi.t, best_zc, [&](int32_t z0, int32_t len) {
             for (const Piece &y : py)
                 for (const Piece &x : px) {
                     Tile t{};
@@ -419,10 +424,11 @@ void make_multi(const Plan &plan, const std::vector<int32_t> *order, int cus, ui
                     t.nxv = x.len;
                     t.y0 = y.at;
                     t.nyv = y.len;
-                    t.z0 = z.at;
-                    t.nzv = z.len;
+                    t.z0 = z0;
+                    t.nzv = len;
                     m->tiles.push_back(t);
                 }
+        });
         m->prefix.push_back((int32_t)m->tiles.size());
     }
     tile_work(m->tiles, &m->work);
