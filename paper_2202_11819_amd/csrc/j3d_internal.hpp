@@ -209,9 +209,9 @@ struct MultiArgs {
 };
 
 // A compiled shape: rows of lanes a tile has along y (64 along x), sweeps per
-// launch, threads, planes of its register ring, workgroups per compute unit.
+// launch, threads, workgroups per compute unit.
 struct MShapeInfo {
-    int rows, t, threads, ring, per_cu;
+    int rows, t, threads, per_cu;
 };
 constexpr int kMultiSegs = 3;  // block rows along z that a tile of unequal blocks may read
 int mshape_count();

@@ -22,12 +22,13 @@
 //     memory access, 0.51 ms with it, 0.56 ms with the boundary tiles.
 //   - Measured and rejected: the x neighbours through the LDS crossbar
 //     (ds_bpermute for one side: 16.2 against 14.2 ms per 100 sweeps of 512^3,
-//     for both 21), deeper prefetch (6 planes in the ring instead of 4: the
-//     same), non-temporal loads (10% slower: the ring cells of a tile are
-//     its neighbours' cells and are found in L2).
+//     for both 21), two more planes of prefetch (the same), non-temporal
+//     loads (10% slower: the ring cells of a tile are its neighbours' cells
+//     and are found in L2).
 //
-// 512^3 as 8^3 blocks of 64^3: 142 us a sweep (945 GLUP/s) against 386 us one
-// sweep per launch; 64^3: 4.1 against 11.6 us; 33x35x31: 3.3 against 11.4 us.
+// 512^3 as 8^3 blocks of 64^3: 138 us a sweep (970 GLUP/s) against 386 us one
+// sweep per launch; 64^3: 4.0 against 11.6 us; 33x35x31: 4.0 against 11.4 us
+// (a sweep's share of a whole checked pass).
 //
 // Each value is the 7-term sum of the same operands in the same order as in a
 // single sweep (centre, x-, x+, y-, y+, z-, z+, each addition rounded, then
@@ -90,12 +91,30 @@ __device__ __forceinline__ double from_above(double v) { return lane_shift<0x130
 // operands instead (64 x 64 tiles: 310 registers instead of 230).
 __device__ __forceinline__ void keep_here(double &v) { asm volatile("" : "+v"(v)); }
 
-// v = b in the lanes of `m`: one move under the execution mask instead of two
-// selects.  Every lane of a wave is active here, so the mask goes back to all
-// ones.  Also keeps v's computation in its place (see the step).
-__device__ __forceinline__ void keep_lanes(double &v, double b, uint64_t m)
+// v[r] = b[r] in the lanes of m[r]: one move under the execution mask instead of
+// two selects.  Every lane of a wave is active here, so the mask goes back to
+// all ones.  Also keeps the values' computation in its place (see the step).
+template <int N>
+__device__ __forceinline__ void keep_lanes(double *v, const double *b, const uint64_t *m)
 {
-    asm volatile("s_mov_b64 exec, %2\n\tv_mov_b64_e32 %0, %1\n\ts_mov_b64 exec, -1" : "+v"(v) : "v"(b), "s"(m));
+    if constexpr (N >= 4) {
+        asm volatile("s_mov_b64 exec, %8\n\tv_mov_b64_e32 %0, %4\n\ts_mov_b64 exec, %9\n\tv_mov_b64_e32 %1, %5\n\t"
+                     "s_mov_b64 exec, %10\n\tv_mov_b64_e32 %2, %6\n\ts_mov_b64 exec, %11\n\tv_mov_b64_e32 %3, %7\n\t"
+                     "s_mov_b64 exec, -1"
+                     : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3])
+                     : "v"(b[0]), "v"(b[1]), "v"(b[2]), "v"(b[3]), "s"(m[0]), "s"(m[1]), "s"(m[2]), "s"(m[3]));
+        keep_lanes<N - 4>(v + 4, b + 4, m + 4);
+    } else if constexpr (N >= 2) {
+        asm volatile("s_mov_b64 exec, %4\n\tv_mov_b64_e32 %0, %2\n\ts_mov_b64 exec, %5\n\tv_mov_b64_e32 %1, %3\n\t"
+                     "s_mov_b64 exec, -1"
+                     : "+v"(v[0]), "+v"(v[1])
+                     : "v"(b[0]), "v"(b[1]), "s"(m[0]), "s"(m[1]));
+        keep_lanes<N - 2>(v + 2, b + 2, m + 2);
+    } else if constexpr (N == 1) {
+        asm volatile("s_mov_b64 exec, %2\n\tv_mov_b64_e32 %0, %1\n\ts_mov_b64 exec, -1"
+                     : "+v"(v[0])
+                     : "v"(b[0]), "s"(m[0]));
+    }
 }
 
 __device__ __forceinline__ void lds_barrier()
@@ -105,10 +124,9 @@ __device__ __forceinline__ void lds_barrier()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-template <int NW_, int RY_, int T_, int NB_>
+template <int NW_, int RY_, int T_>
 struct MShape {
-    static constexpr int NW = NW_, RY = RY_, T = T_, NB = NB_, NT = NW * 64;
-    static_assert(NB % 2 == 0 && NB >= 4, "even ring: the stages' two planes alternate with it");
+    static constexpr int NW = NW_, RY = RY_, T = T_, NT = NW * 64;
 };
 
 // One tile's place in its problem, uniform over the workgroup.
@@ -131,7 +149,7 @@ struct MGeo {
 template <class S, bool GEN, bool EDGE, bool XE, bool RES>
 __device__ __forceinline__ double multi_tile(const MGeo &g, double *E, double *LX, uint32_t *tab, int64_t *xtab)
 {
-    constexpr int NW = S::NW, RY = S::RY, T = S::T, NB = S::NB;
+    constexpr int NW = S::NW, RY = S::RY, T = S::T;
     // Equal blocks: stores stream (non-temporal).  Unequal ones: tiles end inside
     // cache lines, which L2 joins with the neighbour tile's half (640^3 uneven:
     // 22.5 against 22.9 ms per 50 sweeps at T = 4, 17.2 against 17.8 at T = 5).
@@ -162,12 +180,15 @@ __device__ __forceinline__ double multi_tile(const MGeo &g, double *E, double *L
     const int pitchA = blk(0)->pitch, eyA = blk(0)->ext[1];
     const int64_t psA = plane_stride(pitchA, eyA);
     const int64_t delta = blk(0)->off[p ^ 1] - blk(0)->off[p];
-    // bytes a plane's resource spans: the plane itself, or with several blocks
-    // what is left of the arena, as far as 32-bit offsets go
+    // Bytes a plane's resource spans: the plane itself, or with several blocks
+    // what is left of the arena (behind the last plane of the block row, for
+    // equal blocks: the same for all its planes), as far as 32-bit offsets go.
     auto reach = [&](const char *at) __attribute__((always_inline)) -> uint32_t {
-        if (!multi) return (uint32_t)(psA * 8);
         const uint64_t left = (uint64_t)(g.end - at);
         return left < kMaxSpan ? (uint32_t)left : kMaxSpan;
+    };
+    auto row_span = [&](const char *field, int ez) __attribute__((always_inline)) -> uint32_t {
+        return multi ? reach(field + (ez + 1) * psA * 8) : (uint32_t)(psA * 8);
     };
 
     // per-lane byte offsets of this wave's rows from plane lz of block (bxa, bya, bz)
@@ -220,14 +241,18 @@ __device__ __forceinline__ double multi_tile(const MGeo &g, double *E, double *L
         lzl = k0 < 0 ? -1 : g.mz[2 * c + 1];
         ezl = blk(bzl)->ext[2];
     }
-    const char *lp = (const char *)(g.base + blk(bzl)->off[p] + (int64_t)(lzl + 1) * psA);
+    const char *lp = (const char *)(g.base + blk(bzl)->off[p]);
+    uint32_t span_in = row_span(lp, ezl);
+    lp += (int64_t)(lzl + 1) * psA * 8;
     int bzo = 0, lzo = g.z0, ezo = g.nz;
     if (multi) {
         bzo = g.mz[2 * g.z0];
         lzo = g.mz[2 * g.z0 + 1];
         ezo = blk(bzo)->ext[2];
     }
-    char *op = (char *)(g.base + blk(bzo)->off[p] + delta + (int64_t)(lzo + 1) * psA);
+    char *op = (char *)(g.base + blk(bzo)->off[p] + delta);
+    uint32_t span_out = row_span(op, ezo);
+    op += (int64_t)(lzo + 1) * psA * 8;
     if (!GEN) {
         offsets(bzl, vin);
     } else {
@@ -280,17 +305,15 @@ __device__ __forceinline__ double multi_tile(const MGeo &g, double *E, double *L
     }
     const uint64_t xm = __builtin_amdgcn_ballot_w64(isx);
 
-    double R[NB][RY], X[NB] = {};
-    double St[T - 1][2][RY];
+    double St[T][2][RY];       // stage s: planes q-1 and q of iterate t+s, alternating
+    double L[2][RY], X[2] = {};  // planes on their way in, and their x boundary values
 #pragma unroll
-    for (int r = 0; r < RY; ++r) {
-        R[0][r] = R[1][r] = 0.0;
+    for (int r = 0; r < RY; ++r)
 #pragma unroll
-        for (int s = 0; s < T - 1; ++s) St[s][0][r] = St[s][1][r] = 0.0;
-    }
+        for (int s = 0; s < T; ++s) St[s][0][r] = St[s][1][r] = 0.0;
 
     auto load = [&](double (&d)[RY], double &x) __attribute__((always_inline)) {
-        const __amdgpu_buffer_rsrc_t rz = plane_rsrc(lp, zl <= zlast ? reach(lp) : 0u);
+        const __amdgpu_buffer_rsrc_t rz = plane_rsrc(lp, zl <= zlast ? (GEN && multi ? reach(lp) : span_in) : 0u);
 #pragma unroll
         for (int r = 0; r < RY; ++r) d[r] = bload(rz, vin[r]);
         if (XE) x = xb[(uint64_t)xey * (uint32_t)min(max(lzl, 0), ezl - 1)];
@@ -307,7 +330,9 @@ __device__ __forceinline__ double multi_tile(const MGeo &g, double *E, double *L
             ++bzl;
             lzl = 0;
             ezl = blk(bzl)->ext[2];
-            lp = (const char *)(g.base + blk(bzl)->off[p] + psA);
+            lp = (const char *)(g.base + blk(bzl)->off[p]);
+            span_in = row_span(lp, ezl);
+            lp += psA * 8;
             if (GEN) {
 #pragma unroll
                 for (int r = 0; r < RY; ++r) vin[r] = tab[((bzl - bz0) * RY + r) * S::NT + threadIdx.x];
@@ -332,18 +357,23 @@ __device__ __forceinline__ double multi_tile(const MGeo &g, double *E, double *L
         }
     };
 #pragma unroll
-    for (int i = 2; i < NB; ++i) {
-        load(R[i], X[i]);
+    for (int i = 0; i < 2; ++i) {
+        load(L[i], X[i]);
         advance_in();
         no_stores();
     }
 
     double rmax = 0.0;
+    uint32_t zbits = 0;  // bit 31-s: plane k-1-s lies on a z face
+    // stages of a shorter launch that pass their input on, from bit 31 down
+    const uint32_t idle = (uint32_t)(0xffffffff00000000ull >> (T - g.ns));
+    uint64_t xms[RY];
+#pragma unroll
+    for (int r = 0; r < RY; ++r) xms[r] = xm;
     auto step = [&](auto zm, const int k, const int j) __attribute__((always_inline)) {
         constexpr bool ZM = decltype(zm)::value;  // some stage may be on a z face (or idle)
-        double *Ew = E + (j & 1) * (T * NW * 128);
-        const double *Er = E + ((j & 1) ^ 1) * (T * NW * 128);
-        const int ja = j, jb = (j + 1) % NB, jc = (j + 2) % NB, ia = j & 1, ib = ia ^ 1;
+        double *Ew = E + j * (T * NW * 128);
+        const double *Er = E + (j ^ 1) * (T * NW * 128);
         double up[T], dn[T];
         auto read_edges = [&](int s) __attribute__((always_inline)) {
             up[s] = Er[(s * NW + max(w - 1, 0)) * 128 + 64 + lane];
@@ -356,22 +386,23 @@ __device__ __forceinline__ double multi_tile(const MGeo &g, double *E, double *L
             Ew[(s * NW + w) * 128 + 64 + lane] = last;
         };
         auto part = [&](int s, int r) __attribute__((always_inline)) {
-            const double(&A)[RY] = s == 0 ? R[ja] : St[s == 0 ? 0 : s - 1][ia];
-            const double(&B)[RY] = s == 0 ? R[jb] : St[s == 0 ? 0 : s - 1][ib];
+            const double(&B)[RY] = St[s][j ^ 1];
             double t = B[r];
             t += from_below(B[r]);
             t += from_above(B[r]);
             t += r > 0 ? B[r > 0 ? r - 1 : 0] : up[s];
             t += r < RY - 1 ? B[r < RY - 1 ? r + 1 : r] : dn[s];
-            t += A[r];
+            t += St[s][j][r];
             return t;
         };
+        if (ZM) zbits = zbits >> 1 | ((uint32_t)((k - 1) | (g.nz - k)) & 0x80000000u);
+        const uint32_t still = (uint32_t)__builtin_amdgcn_readfirstlane((int)(zbits | idle));
         double pa[RY], W[RY];
 #pragma unroll
         for (int r = 0; r < RY; ++r) pa[r] = part(0, r);
 #pragma unroll
         for (int s = 0; s < T; ++s) {
-            double pn[RY];
+            double pn[RY], v[RY];
             if (s + 2 < T) read_edges(s + 2);
             if (s + 1 < T) {
 #pragma unroll
@@ -379,43 +410,51 @@ __device__ __forceinline__ double multi_tile(const MGeo &g, double *E, double *L
             }
             if (s == 0) {
                 if (XE) {
-                    LX[w * 64 + lane] = X[jc];
+                    double xv[RY];
+                    LX[w * 64 + lane] = X[j];
 #pragma unroll
-                    for (int r = 0; r < RY; ++r) keep_lanes(R[jc][r], LX[w * 64 + (gx < 0 ? 0 : 32) + r], xm);
+                    for (int r = 0; r < RY; ++r) xv[r] = LX[w * 64 + (gx < 0 ? 0 : 32) + r];
+                    keep_lanes<RY>(L[j], xv, xms);
                 }
-                edges(0, R[jc][0], R[jc][RY - 1]);
+#pragma unroll
+                for (int r = 0; r < RY; ++r) St[0][j][r] = L[j][r];
+                edges(0, L[j][0], L[j][RY - 1]);
             }
             const int q = k - 1 - s;  // the plane this stage computes
-            const int zi = ZM ? (q >> 31) | ((g.nz - 1 - q) >> 31) | ((s - T + g.ns) >> 31) : 0;
-            const uint64_t zf = (uint64_t)(int64_t)zi;
+#pragma unroll
+            for (int r = 0; r < RY; ++r) v[r] = (pa[r] + St[s][j][r]) * kW;
+            if (EDGE || ZM) {
+                const uint64_t zf = ZM && (still << s & 0x80000000u) ? ~0ull : 0ull;
+                uint64_t m[RY];
+#pragma unroll
+                for (int r = 0; r < RY; ++r) m[r] = zf | (EDGE ? fixrow(r) : 0ull);
+                keep_lanes<RY>(v, St[s][j ^ 1], m);
+            } else {
+#pragma unroll
+                for (int r = 0; r < RY; ++r) keep_here(v[r]);
+            }
+            if (RES && s == T - 1 && q >= g.z0 && q < g.z0 + g.nzv) {
+#pragma unroll
+                for (int r = 0; r < RY; ++r) {
+                    const double d = (vlane | srow(r)) == 0u ? fabs(v[r] - St[s][j ^ 1][r]) : 0.0;
+                    rmax = d > rmax ? d : rmax;
+                }
+            }
 #pragma unroll
             for (int r = 0; r < RY; ++r) {
-                const double c = s == 0 ? R[jc][r] : St[s == 0 ? 0 : s - 1][ia][r];
-                double v = (pa[r] + c) * kW;
-                if (EDGE || ZM || RES) {
-                    const double b = s == 0 ? R[jb][r] : St[s == 0 ? 0 : s - 1][ib][r];
-                    if (EDGE || ZM)
-                        keep_lanes(v, b, zf | (EDGE ? fixrow(r) : 0ull));
-                    if (RES && s == T - 1 && q >= g.z0 && q < g.z0 + g.nzv) {
-                        const double d = (vlane | srow(r)) == 0u ? fabs(v - b) : 0.0;
-                        rmax = d > rmax ? d : rmax;
-                    }
-                }
-                if (!EDGE && !ZM) keep_here(v);
                 if (s < T - 1)
-                    St[s < T - 1 ? s : 0][ia][r] = v;
+                    St[s < T - 1 ? s + 1 : s][j][r] = v[r];
                 else
-                    W[r] = v;
+                    W[r] = v[r];
+                pa[r] = pn[r];
             }
-            if (s == 0) load(R[ja], X[ja]);
-            if (s < T - 1) edges(s + 1, St[s < T - 1 ? s : 0][ia][0], St[s < T - 1 ? s : 0][ia][RY - 1]);
-#pragma unroll
-            for (int r = 0; r < RY; ++r) pa[r] = pn[r];
-            }
+            if (s == 0) load(L[j], X[j]);
+            if (s < T - 1) edges(s + 1, v[0], v[RY - 1]);
+        }
         advance_in();
         const int q = k - T;
         const bool st = q >= g.z0 && q < g.z0 + g.nzv;
-        const __amdgpu_buffer_rsrc_t ro = plane_rsrc(op, st ? reach(op) : 0u);
+        const __amdgpu_buffer_rsrc_t ro = plane_rsrc(op, st ? (GEN && multi ? reach(op) : span_out) : 0u);
 #pragma unroll
         for (int r = 0; r < RY; ++r) bstore<kStore>(ro, GEN ? vout[GEN ? r : 0] : vin[r] | vlane | srow(r), W[r]);
         if (st) {
@@ -429,31 +468,32 @@ __device__ __forceinline__ double multi_tile(const MGeo &g, double *E, double *L
                 ++bzo;
                 lzo = 0;
                 ezo = blk(bzo)->ext[2];
-                op = (char *)(g.base + blk(bzo)->off[p] + delta + psA);
+                op = (char *)(g.base + blk(bzo)->off[p] + delta);
+                span_out = row_span(op, ezo);
+                op += psA * 8;
             }
         }
         lds_barrier();
     };
 
+    // Two steps a round: the planes' registers alternate.  The arriving plane is
+    // moved into place (2% more instructions) so that two steps suffice: with
+    // its registers rotating as well a round was four, and fetching that code
+    // cost a small launch up to 9 us (157x211x183: 1370 against 1311 us for 30
+    // launches; 64^3: 467 against 415 us for 25; 512^3: 15.1 against 14.5 ms).
     int k = k0;
+    auto round = [&](auto zm) __attribute__((always_inline)) {
+        step(zm, k, 0);
+        step(zm, k + 1, 1);
+        k += 2;
+    };
     if (!EDGE && g.ns == T) {
-
-        for (; k < T && k <= k1; k += NB) {
-#pragma unroll
-            for (int j = 0; j < NB; ++j) step(std::true_type{}, k + j, j);
-        }
-        const int kf = min(k1, g.nz - (NB - 1));
-
-        for (; k <= kf; k += NB) {
-#pragma unroll
-            for (int j = 0; j < NB; ++j) step(std::false_type{}, k + j, j);
-        }
+        while (k < T && k <= k1) round(std::true_type{});
+        const int kf = min(k1, g.nz - 1);
+        while (k <= kf) round(std::false_type{});
+        zbits = 0;  // the planes computed so far lie inside
     }
-
-    for (; k <= k1; k += NB) {
-#pragma unroll
-        for (int j = 0; j < NB; ++j) step(std::true_type{}, k + j, j);
-    }
+    while (k <= k1) round(std::true_type{});
     return rmax;
 }
 
@@ -536,34 +576,33 @@ __global__ __launch_bounds__(S::NT)  void multisweep_kernel(MultiArgs a)
     }
 }
 
-// Shapes: waves, rows per thread, sweeps, planes in the register ring,
-// workgroups that fit a compute unit (by registers and LDS).  The planner
+// Shapes: waves, rows per thread, sweeps, workgroups that fit a compute unit (by registers and LDS).  The planner
 // picks by estimated time (multi_cost); each is the fastest somewhere:
 // 64 x 64 lanes and T = 4 on large equal blocks, 64 x 48 and T = 5 where
 // memory is slow (ragged widths), fewer rows where the grid is too small to
 // give every compute unit a tile, T = 3 where the ring of small problems eats
 // the gain of a fourth sweep (a batch of 32..256-wide grids).
 #define J3D_MSHAPES(M) \
-    M(8, 8, 4, 4, 1)   \
-    M(8, 6, 4, 4, 1)   \
-    M(8, 6, 5, 4, 1)   \
-    M(8, 4, 4, 4, 1)   \
-    M(8, 4, 3, 4, 2)   \
-    M(8, 3, 4, 4, 2)   \
-    M(8, 2, 4, 4, 2)
+    M(8, 8, 4, 1)   \
+    M(8, 6, 4, 1)   \
+    M(8, 6, 5, 1)   \
+    M(8, 4, 4, 1)   \
+    M(8, 4, 3, 2)   \
+    M(8, 3, 4, 2)   \
+    M(8, 2, 4, 2)
 
 struct MEntry {
-    int nw, ry, t, nb, per_cu;
+    int nw, ry, t, per_cu;
     void (*fn)(MultiArgs);
     void (*gen)(MultiArgs);
 };
-#define M(NW, RY, T, NB, PC) {NW, RY, T, NB, PC, multisweep_kernel<MShape<NW, RY, T, NB>, false>, multisweep_kernel<MShape<NW, RY, T, NB>, true>},
+#define M(NW, RY, T, PC) {NW, RY, T, PC, multisweep_kernel<MShape<NW, RY, T>, false>, multisweep_kernel<MShape<NW, RY, T>, true>},
 const MEntry kM[] = {J3D_MSHAPES(M)};
 #undef M
 }  // namespace
 
 int mshape_count() { return (int)(sizeof kM / sizeof kM[0]); }
-MShapeInfo mshape_info(int i) { return MShapeInfo{kM[i].nw * kM[i].ry, kM[i].t, kM[i].nw * 64, kM[i].nb, kM[i].per_cu}; }
+MShapeInfo mshape_info(int i) { return MShapeInfo{kM[i].nw * kM[i].ry, kM[i].t, kM[i].nw * 64, kM[i].per_cu}; }
 
 int launch_multisweep(int shape, bool general, const MultiArgs &a, int grid, void *stream)
 {

@@ -259,11 +259,10 @@ uint64_t multi_tiles_bound(const Plan &plan)
     return best;
 }
 
-// Plane steps of a tile: its planes, the ramp on both sides, whole rounds of
-// the register ring.
+// Plane steps of a tile: its planes and the ramp on both sides, in rounds of two.
 int64_t multi_steps(const MShapeInfo &mi, int64_t planes)
 {
-    return ceil_div(planes + 2 * mi.t, mi.ring) * mi.ring;
+    return (planes + 2 * mi.t + 1) / 2 * 2;
 }
 
 // Estimated microseconds per sweep of a launch of `tiles` tiles of `steps`
@@ -383,7 +382,7 @@ void make_multi(const Plan &plan, const std::vector<int32_t> *order, int cus, ui
             ok = multi_span_ok(plan, pp, px, py, mi.t);
         }
         int last_zc = 0;
-        for (int64_t nc = 1; ok && nc <= ceil_div(depth, kMinMultiZ); nc += 1 + nc / 8) {
+        for (int64_t nc = 1; ok && nc <= ceil_div(depth, kMinMultiZ); nc += 1 + (count > 1 ? nc / 8 : nc / 16)) {
             const int zc = (int)ceil_div(depth, nc);
             if (zc == last_zc) continue;
             last_zc = zc;
