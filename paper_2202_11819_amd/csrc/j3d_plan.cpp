@@ -332,17 +332,16 @@ namespace {
 // z pieces of a problem: near-equal, at most zc planes.  With unequal blocks
 // (general) each lies in one block row, and the rows are at least t deep, so a
 // tile reads its own row and its two neighbours at most.  Calls
-// piece(start, planes) for each; false if a row is too shallow.
+// cut(start, planes, pieces) for each uncut stretch, whose piece i starts at
+// i * planes / pieces; false if a row is too shallow.
 template <class F>
-bool cut_z(const ProbPlan &pp, bool general, int t, int zc, F piece)
+bool cut_z(const ProbPlan &pp, bool general, int t, int zc, F cut)
 {
     const bool rows = general && pp.nblocks > 1;
     for (int32_t b = 0; b < (rows ? pp.d.nb[2] : 1); ++b) {
         const int64_t at = rows ? pp.d.org[2][b] : 0, len = rows ? pp.d.ext[2][b] : pp.d.n[2];
         if (rows && len < t) return false;
-        const int64_t n = ceil_div(len, zc);
-        for (int64_t i = 0; i < n; ++i)
-            piece((int32_t)(at + i * len / n), (int32_t)((i + 1) * len / n - i * len / n));
+        cut(at, len, ceil_div(len, zc));
     }
     return true;
 }
@@ -391,9 +390,11 @@ void make_multi(const Plan &plan, const std::vector<int32_t> *order, int cus, ui
             double tiles = 0, steps = 0, cells = 0, cost = 0;
             for (int32_t k = 0; k < count && ok; ++k) {
                 const ProbPlan &pp = prob(k);
-                ok = cut_z(pp, m->general, mi.t, zc, [&](int32_t, int32_t len) {
-                    tiles += (double)xy[k];
-                    steps += (double)xy[k] * multi_steps(mi, len);
+                ok = cut_z(pp, m->general, mi.t, zc, [&](int64_t, int64_t len, int64_t n) {
+                    // n pieces: len % n of them a plane deeper than the others
+                    tiles += (double)(xy[k] * n);
+                    steps += (double)(xy[k] * (len % n * multi_steps(mi, len / n + 1) +
+                                               (n - len % n) * multi_steps(mi, len / n)));
                 });
                 cells += (double)pp.d.n[0] * pp.d.n[1] * pp.d.n[2];
                 const double sweeps = k + 1 < count ? (double)(pp.iters - prob(k + 1).iters)
@@ -414,19 +415,20 @@ void make_multi(const Plan &plan, const std::vector<int32_t> *order, int cus, ui
         const ProbPlan &pp = prob(k);
         cut_axis((int32_t)pp.d.n[0], 64, mi.t, x_align(pp), &px);
         cut_axis((int32_t)pp.d.n[1], mi.rows, mi.t, 1, &py);
-        cut_z(pp, m->general, mi.t, best_zc, [&](int32_t z0, int32_t len) {
-            for (const Piece &y : py)
-                for (const Piece &x : px) {
-                    Tile t{};
-                    t.block = pp.block_begin;
-                    t.x0 = x.at;
-                    t.nxv = x.len;
-                    t.y0 = y.at;
-                    t.nyv = y.len;
-                    t.z0 = z0;
-                    t.nzv = len;
-                    m->tiles.push_back(t);
-                }
+        cut_z(pp, m->general, mi.t, best_zc, [&](int64_t at, int64_t len, int64_t n) {
+            for (int64_t i = 0; i < n; ++i)
+                for (const Piece &y : py)
+                    for (const Piece &x : px) {
+                        Tile t{};
+                        t.block = pp.block_begin;
+                        t.x0 = x.at;
+                        t.nxv = x.len;
+                        t.y0 = y.at;
+                        t.nyv = y.len;
+                        t.z0 = (int32_t)(at + i * len / n);
+                        t.nzv = (int32_t)((i + 1) * len / n - i * len / n);
+                        m->tiles.push_back(t);
+                    }
         });
         m->prefix.push_back((int32_t)m->tiles.size());
     }

@@ -52,32 +52,35 @@ const BlockDesc *dblocks(const Plan &plan, char *arena)
 
 }  // namespace
 
-j3d_status upload_tables(const Plan &plan, char *arena, hipStream_t stream)
+j3d_status upload_tables(const Plan &plan, const std::vector<Tile> &tiles, const MultiPlan &m, char *arena,
+                         hipStream_t stream)
 {
-    hipError_t e = hipMemcpyAsync(arena + plan.off_blocks, plan.blocks.data(),
-                                  plan.blocks.size() * sizeof(BlockDesc), hipMemcpyHostToDevice, stream);
-    if (e != hipSuccess) return hip_status(e, "upload blocks");
+    if (tiles.size() > plan.tiles_cap || m.tiles.size() > plan.mtiles_cap)
+        return set_error(J3D_EINVAL, "tile table overflow");
     std::vector<ProbDesc> probs(plan.probs.size());
     for (size_t i = 0; i < probs.size(); ++i) fill_prob(plan, (int32_t)i, 0, &probs[i]);
-    e = hipMemcpyAsync(arena + plan.off_probs, probs.data(), probs.size() * sizeof(ProbDesc),
-                       hipMemcpyHostToDevice, stream);
-    if (e != hipSuccess) return hip_status(e, "upload problems");
+    // the problems' maps follow one another in the arena: one image of them all
+    const uint64_t maps_at = plan.probs.front().maps_off;
     std::vector<int32_t> maps;
     for (const ProbPlan &pp : plan.probs) {
-        maps.clear();
+        maps.resize((pp.maps_off - maps_at) / sizeof(int32_t), 0);
         for (int a = 0; a < 3; ++a)
             for (int32_t b = 0; b < pp.d.nb[a]; ++b)
                 for (int64_t l = 0; l < pp.d.ext[a][b]; ++l) {
                     maps.push_back(b);
                     maps.push_back((int32_t)l);
                 }
-        e = hipMemcpyAsync(arena + pp.maps_off, maps.data(), maps.size() * sizeof(int32_t),
-                           hipMemcpyHostToDevice, stream);
-        if (e != hipSuccess) return hip_status(e, "upload maps");
-        e = hipStreamSynchronize(stream);  // `maps` is reused
-        if (e != hipSuccess) return hip_status(e, "upload maps");
     }
-    return hip_status(hipStreamSynchronize(stream), "upload tables");
+    auto copy = [&](uint64_t at, const void *src, uint64_t bytes) {
+        return bytes ? hipMemcpyAsync(arena + at, src, bytes, hipMemcpyHostToDevice, stream) : hipSuccess;
+    };
+    hipError_t e = copy(plan.off_blocks, plan.blocks.data(), plan.blocks.size() * sizeof(BlockDesc));
+    if (e == hipSuccess) e = copy(plan.off_probs, probs.data(), probs.size() * sizeof(ProbDesc));
+    if (e == hipSuccess) e = copy(plan.off_tiles, tiles.data(), tiles.size() * sizeof(Tile));
+    if (e == hipSuccess && m.shape >= 0) e = copy(plan.off_mtiles, m.tiles.data(), m.tiles.size() * sizeof(Tile));
+    if (e == hipSuccess) e = copy(maps_at, maps.data(), maps.size() * sizeof(int32_t));
+    const hipError_t w = hipStreamSynchronize(stream);  // the host copies end here, also after an error
+    return hip_status(e != hipSuccess ? e : w, "upload tables");
 }
 
 j3d_status upload_tiles(const Plan &plan, const std::vector<Tile> &tiles, char *arena,
@@ -85,16 +88,6 @@ j3d_status upload_tiles(const Plan &plan, const std::vector<Tile> &tiles, char *
 {
     if (tiles.size() > plan.tiles_cap) return set_error(J3D_EINVAL, "tile table overflow");
     hipError_t e = hipMemcpyAsync(arena + plan.off_tiles, tiles.data(), tiles.size() * sizeof(Tile),
-                                  hipMemcpyHostToDevice, stream);
-    if (e != hipSuccess) return hip_status(e, "upload tiles");
-    return hip_status(hipStreamSynchronize(stream), "upload tiles");
-}
-
-j3d_status upload_multi(const Plan &plan, const MultiPlan &m, char *arena, hipStream_t stream)
-{
-    if (m.shape < 0) return J3D_OK;
-    if (m.tiles.size() > plan.mtiles_cap) return set_error(J3D_EINVAL, "tile table overflow");
-    hipError_t e = hipMemcpyAsync(arena + plan.off_mtiles, m.tiles.data(), m.tiles.size() * sizeof(Tile),
                                   hipMemcpyHostToDevice, stream);
     if (e != hipSuccess) return hip_status(e, "upload tiles");
     return hip_status(hipStreamSynchronize(stream), "upload tiles");
@@ -236,7 +229,7 @@ void drop_graphs(j3d_solver *s)
     s->graphs.clear();
 }
 
-j3d_status apply_tune(j3d_solver *s, const j3d_tune &t)
+j3d_status apply_tune(j3d_solver *s, const j3d_tune &t, bool upload = true)
 {
     int zc = 0;
     j3d_status st = check_tune(s->plan, &t, &zc);
@@ -244,7 +237,7 @@ j3d_status apply_tune(j3d_solver *s, const j3d_tune &t)
     std::vector<Tile> tiles;
     std::vector<int32_t> first;
     make_tiles(s->plan, 0, (int32_t)s->plan.blocks.size(), t.variant, t.zchunk, &tiles, &first);
-    st = upload_tiles(s->plan, tiles, s->arena, s->stream);
+    if (upload) st = upload_tiles(s->plan, tiles, s->arena, s->stream);
     if (st != J3D_OK) return st;
     s->tune = t;
     s->zchunk = zc;
@@ -694,15 +687,12 @@ j3d_status j3d_create(const j3d_problem *p, void *dev_arena, uint64_t arena_byte
     s->stream = static_cast<hipStream_t>(hip_stream);
     s->device = dev;
     s->cus = cus;
-    st = upload_tables(s->plan, s->arena, s->stream);
-    if (st == J3D_OK) {
-        j3d_tune t;
-        default_tune(s->plan, s->cus, &t);
-        st = apply_tune(s, t);
-    }
+    j3d_tune t;
+    default_tune(s->plan, s->cus, &t);
+    st = apply_tune(s, t, false);
     if (st == J3D_OK) {
         make_multi(s->plan, nullptr, s->cus, s->plan.mtiles_cap, &s->multi);
-        st = upload_multi(s->plan, s->multi, s->arena, s->stream);
+        st = upload_tables(s->plan, s->tiles, s->multi, s->arena, s->stream);
     }
     if (st == J3D_OK)
         st = hip_status(launch_fill_u32(reinterpret_cast<unsigned int *>(s->arena + s->plan.off_queue), 16, 0,
@@ -978,9 +968,7 @@ j3d_status j3d_batch_create(int32_t count, const j3d_problem *probs, const int64
     }
     b->max_iters = count > 0 ? iters[b->order[0]] : 0;
     tile_work(tiles, &b->work);
-    st = upload_tables(b->plan, b->arena, b->stream);
-    if (st == J3D_OK) st = upload_tiles(b->plan, tiles, b->arena, b->stream);
-    if (st == J3D_OK) st = upload_multi(b->plan, b->multi, b->arena, b->stream);
+    st = upload_tables(b->plan, tiles, b->multi, b->arena, b->stream);
     if (st == J3D_OK)
         st = hip_status(launch_fill_u32(reinterpret_cast<unsigned int *>(b->arena + b->plan.off_queue), 16, 0,
                                         b->stream),
