@@ -506,7 +506,7 @@ def main():
     ap.add_argument("--no-copy", action="store_true")
     ap.add_argument("--headline-only", action="store_true",
                     help="default workload: only the 512^3 line (no modes, decompositions, batched or served records)")
-    ap.add_argument("--batch-two-sweep", action="store_true", help="batch workload: also two sweeps per launch")
+    ap.add_argument("--batch-two-sweep", action="store_true", help="batch workload: also several sweeps per launch asked for")
     ap.add_argument("--cpu-seconds", type=float, default=15.0)
     ap.add_argument("--requests", type=int, default=1100, help="serve workload: number of requests")
     ap.add_argument("--serve-dump", default="", help="serve workload: write per-request records here")
@@ -520,9 +520,9 @@ def main():
                     help="serve workload: stop a request at the first residual check with r <= tol (0: never)")
     ap.add_argument("--fill-cells", type=int, default=-1, help="serve workload: pool round policy (-1: default)")
     ap.add_argument("--pool-tune", default="", help="serve workload: variant,zchunk of the pool's rounds")
-    ap.add_argument("--pool-two-sweep", action="store_true", help="serve workload: two sweeps per launch in the pool")
+    ap.add_argument("--pool-two-sweep", action="store_true", help="serve workload: several sweeps per launch in the pool whatever its tune")
     ap.add_argument("--serial-two-sweep", action="store_true",
-                    help="serve workload: the serial baseline solves with two sweeps per launch")
+                    help="serve workload: the serial baseline solves in mode two_sweep")
     ap.add_argument("--backlog-share", type=int, default=-1,
                     help="serve workload: rounds hold at least 1/k of the running cells (-1: default)")
     ap.add_argument("--odf-edge", type=int, default=256, help="odf workload: grid edge")

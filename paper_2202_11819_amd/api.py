@@ -84,7 +84,8 @@ class Solver:
 
 
 class Batch:
-    """Many independent problems advanced by one launch per sweep."""
+    """Many independent problems advanced by one launch for all of them (several
+    sweeps each; one with a tune that names a shape)."""
 
     def __init__(self, problems, iters, tune=None, stream=None, device="cuda"):
         self.problems = list(problems)
@@ -188,7 +189,8 @@ class Pool:
         C.j3d_pool_set_tune(self.h, variant, zchunk)
 
     def set_two_sweep(self, enable=True):
-        """Two sweeps per launch in the rounds; only while no request is admitted."""
+        """Several sweeps per launch in the rounds, also after set_tune; only while no
+        request is admitted."""
         C.j3d_pool_set_two_sweep(self.h, enable)
 
     def poll(self):

@@ -41,7 +41,8 @@ def serve_pool(trace, budget_bytes, max_slots=256, round_sweeps=50, check_every=
                keep_results=False, log=None, fill_cells=None, tune=None, backlog_share=None, two_sweep=False):
     """Serve `trace` (list of workloads.Request) in real time; per-request records.
     fill_cells, backlog_share: round policy, tune: (variant, zchunk) of the
-    rounds (None keeps the library defaults), two_sweep: two sweeps per launch."""
+    rounds (None keeps the library defaults), two_sweep: several sweeps
+    per launch whatever the tune."""
     pool = Pool(budget_bytes, max_slots=max_slots)
     if two_sweep:
         pool.set_two_sweep(True)
@@ -214,7 +215,7 @@ def bench_serve(args):
 
 
 def batch_bench(tune=None, retune=False, batch_only=False, two_sweep=False, loop=True, log=_log):
-    """Batched workload: 256 problems in one launch per sweep (autotuned shape,
+    """Batched workload: 256 problems in one launch for all (autotuned shape,
     or `tune`) against the same problems solved one after another with the
     plain solver.  Returns the benchmark record (a dict)."""
     from .autotune import tune_batch
@@ -245,7 +246,7 @@ def batch_bench(tune=None, retune=False, batch_only=False, two_sweep=False, loop
 
     timed_batch(tune)
     tb = min(timed_batch(tune) for _ in range(2))
-    out = {"metric": "batched FP64 Jacobi3D GLUP/s (256 problems, one launch per sweep)",
+    out = {"metric": "batched FP64 Jacobi3D GLUP/s (256 problems, one launch for all)",
            "value": round(lups / tb / 1e9, 2), "unit": "GLUP/s", "higher_is_better": True,
            "batched_s": round(tb, 4), "tune": list(tune), "tile": tile,
            "autotune": search,
@@ -255,7 +256,7 @@ def batch_bench(tune=None, retune=False, batch_only=False, two_sweep=False, loop
     if batch_only:
         return out
     if two_sweep:
-        # the same batch with two sweeps per launch (all problems are undivided)
+        # the same batch with several sweeps per launch asked for (all problems are undivided)
         timed_batch(tune, True)
         t2 = min(timed_batch(tune, True) for _ in range(2))
         out["two_sweep_batched_s"] = round(t2, 4)
