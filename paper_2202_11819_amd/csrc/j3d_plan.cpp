@@ -275,6 +275,8 @@ int64_t multi_steps(const MShapeInfo &mi, int64_t planes)
 //   - memory moves 17 bytes per cell and launch at 5.3 TB/s, at 3.2 TB/s where
 //     tiles end inside cache lines and the grid is past the last-level cache;
 //   - the two overlap only in part: the third root of the sum of cubes.
+// Constants refitted to 5200 timings of 47 grids, with four other shapes,
+// measured 0.996 of the speed over 22 solves, batches and pools: not kept.
 double multi_cost(const MShapeInfo &mi, int cus, double tiles, double steps, double cells, bool ragged)
 {
     const double c = std::min<double>(mi.per_cu, std::ceil(tiles / cus));  // workgroups sharing a compute unit
