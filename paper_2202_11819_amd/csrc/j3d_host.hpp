@@ -190,10 +190,12 @@ struct MultiPlan {
 struct Piece {
     int32_t at, len;
 };
-// Cuts [0, n) into near-equal pieces that fit `cap` lanes or rows with their
-// halo (T cells, or the one boundary cell at the ends of the axis); starts
-// are multiples of `align`.
+// Cuts [0, n) into as few pieces as fit `cap` lanes or rows with their halo (T
+// cells, or the one boundary cell at the ends of the axis), starts on multiples
+// of `align` (1, or 8 where n is a multiple of it).  cut_axis_count is their
+// number.
 void cut_axis(int32_t n, int cap, int t, int align, std::vector<Piece> *out);
+int32_t cut_axis_count(int32_t n, int cap, int t, int align);
 
 // Shape and tiles for problems order[0], order[1], ... of the plan (all in table
 // order if order is NULL), chosen by estimated time; at most `cap` tiles.

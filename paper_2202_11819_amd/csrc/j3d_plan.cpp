@@ -206,29 +206,49 @@ uint64_t count_tiles(const Plan &plan, int variant, int zchunk)
     return n;
 }
 
+// The end pieces have the ring on one side only and one boundary cell on the
+// other, so they can hold t - 1 cells more than the inner ones.
+int32_t cut_axis_count(int32_t n, int cap, int t, int align)
+{
+    if (n <= cap - 2) return 1;
+    const int32_t inner = (cap - 2 * t) / align * align, end = (cap - t - 1) / align * align;
+    return (int32_t)(2 + std::max<int64_t>(0, ((int64_t)n - 2 * end + inner - 1) / inner));
+}
+
 void cut_axis(int32_t n, int cap, int t, int align, std::vector<Piece> *out)
 {
-    out->clear();
-    const int inner = cap - 2 * t, end = cap - t - 1;
-    int m = n <= cap - 2 ? 1 : n <= 2 * end ? 2 : 2 + (n - 2 * end + inner - 1) / inner;
-    for (;; ++m) {
+    const int32_t m = cut_axis_count(n, cap, t, align);
+    out->assign(1, Piece{0, n});
+    if (m == 1) return;
+    // Where all m pieces fit so, end pieces t - 1 cells shorter than the inner
+    // ones: boundary tiles take longer (512^3, 10 x 10 tiles: 13.78 ms per 100
+    // sweeps against 13.95 with end pieces the longer ones).
+    auto shorter_ends = [&](int32_t i) {
+        const int64_t at = i * ((int64_t)n + 2 * (t - 1)) / m - (t - 1);
+        return (int32_t)((at + align / 2) / align * align);
+    };
+    // Else end pieces t - 1 cells longer, which always fits; with starts on
+    // multiples of `align`, pieces of an even multiple (a whole number of cache
+    // lines for align 8) or one more: a start inside a line splits it between tiles.
+    const int32_t units = n / align, inner = (cap - 2 * t) / align;
+    const int32_t even = std::min(inner / 2 * 2, ((units + m - 1) / m + 1) / 2 * 2);
+    const int32_t extra = units - even * m;  // pieces one unit longer: pairs first, an odd one last
+    const int32_t first = extra <= 0 ? 0 : inner > even ? extra / 2 * 2 : extra - 1;
+    auto longer_ends = [&](int32_t i) {
+        if (align == 1) return (int32_t)(i * ((int64_t)n - 2 * (t - 1)) / m + (t - 1));
+        return (even * i + std::min(i, first)) * align;
+    };
+    auto cut = [&](auto start) {
         out->clear();
-        bool ok = true;
-        int32_t at = 0;
-        for (int i = 0; i < m && ok; ++i) {
-            int32_t next = n;
-            if (i + 1 < m) {
-                // the end pieces hold t - 1 cells more: they need no ring there
-                next = (int32_t)((int64_t)(i + 1) * (n + 2 * (t - 1)) / m) - (t - 1);
-                next = (next + align / 2) / align * align;
-            }
-            const int32_t len = next - at;
-            ok = len >= 1 && len + std::min(t, at + 1) + std::min(t, n - next + 1) <= cap;
+        for (int32_t i = 0, at = 0; i < m; ++i) {
+            const int32_t next = i + 1 < m ? start(i + 1) : n, len = next - at;
+            if (len < 1 || len + std::min(t, at + 1) + std::min(t, n - next + 1) > cap) return false;
             out->push_back({at, len});
             at = next;
         }
-        if (ok) return;
-    }
+        return true;
+    };
+    if (!cut(shorter_ends)) cut(longer_ends);
 }
 
 namespace {
@@ -245,14 +265,12 @@ int x_align(const ProbPlan &pp)
 uint64_t multi_tiles_bound(const Plan &plan)
 {
     uint64_t best = 0;
-    std::vector<Piece> px, py;
     for (int s = 0; s < mshape_count(); ++s) {
         const MShapeInfo mi = mshape_info(s);
         uint64_t n = 0;
         for (const ProbPlan &pp : plan.probs) {
-            cut_axis((int32_t)pp.d.n[0], 64, mi.t, x_align(pp), &px);
-            cut_axis((int32_t)pp.d.n[1], mi.rows, mi.t, 1, &py);
-            n += px.size() * py.size() * (uint64_t)ceil_div(pp.d.n[2], kMinMultiZ);
+            n += (uint64_t)cut_axis_count((int32_t)pp.d.n[0], 64, mi.t, x_align(pp)) *
+                 cut_axis_count((int32_t)pp.d.n[1], mi.rows, mi.t, 1) * ceil_div(pp.d.n[2], kMinMultiZ);
         }
         best = std::max(best, n);
     }
