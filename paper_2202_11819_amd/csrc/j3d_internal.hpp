@@ -209,9 +209,10 @@ struct MultiArgs {
 };
 
 // A compiled shape: rows of lanes a tile has along y (64 along x), sweeps per
-// launch, threads, workgroups per compute unit.
+// launch, threads; workgroups per compute unit and bytes of LDS with blocks of
+// equal extents [0] and unequal ones [1].
 struct MShapeInfo {
-    int rows, t, threads, per_cu;
+    int rows, t, threads, per_cu[2], lds[2];
 };
 constexpr int kMultiSegs = 3;  // block rows along z that a tile of unequal blocks may read
 int mshape_count();

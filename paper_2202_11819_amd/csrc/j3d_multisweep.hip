@@ -127,6 +127,15 @@ __device__ __forceinline__ void lds_barrier()
 template <int NW_, int RY_, int T_>
 struct MShape {
     static constexpr int NW = NW_, RY = RY_, T = T_, NT = NW * 64;
+    // Shared memory of a workgroup, in elements: edge rows (both halves of the
+    // double buffer), x boundary values, the residual's wave maxima; and for
+    // blocks of unequal extents the lane offsets and x sources per block row.
+    static constexpr int kEdge = 2 * T * NW * 128, kX = NW * 64, kRed = NW;
+    static constexpr int kTab = kMultiSegs * NT * RY, kXTab = kMultiSegs * NT;
+    static constexpr int lds(bool general)
+    {
+        return (kEdge + kX + kRed) * 8 + (general ? kTab * 4 + kXTab * 8 : 0);
+    }
 };
 
 // One tile's place in its problem, uniform over the workgroup.
@@ -501,11 +510,11 @@ template <class S, bool GEN>
 __global__ __launch_bounds__(S::NT)  void multisweep_kernel(MultiArgs a)
 {
     constexpr int NW = S::NW, T = S::T;
-    __shared__ double E[2 * T * NW * 128];
-    __shared__ double LX[NW * 64];
-    __shared__ double red[NW];
-    __shared__ uint32_t tab[GEN ? kMultiSegs * S::NT * S::RY : 1];
-    __shared__ int64_t xtab[GEN ? kMultiSegs * S::NT : 1];
+    __shared__ double E[S::kEdge];
+    __shared__ double LX[S::kX];
+    __shared__ double red[S::kRed];
+    __shared__ uint32_t tab[GEN ? S::kTab : 1];
+    __shared__ int64_t xtab[GEN ? S::kXTab : 1];
     const int xcd = blockIdx.x % kXcdCount, jj = blockIdx.x / kXcdCount;
     typedef const __attribute__((address_space(4))) char kchar;
     const kint32 *xc = (const kint32 *)((kchar *)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(MultiArgs, xcut));
@@ -576,33 +585,37 @@ __global__ __launch_bounds__(S::NT)  void multisweep_kernel(MultiArgs a)
     }
 }
 
-// Shapes: waves, rows per thread, sweeps, workgroups that fit a compute unit (by registers and LDS).  The planner
+// Shapes: waves, rows per thread, sweeps, workgroups that fit a compute unit
+// with equal and with unequal blocks (by registers, and by the 160 KB of LDS:
+// the general kernels' tables leave room for one).  The planner
 // picks by estimated time (multi_cost); each is the fastest somewhere:
 // 64 x 64 lanes and T = 4 on large equal blocks, 64 x 48 and T = 5 where
 // memory is slow (ragged widths), fewer rows where the grid is too small to
 // give every compute unit a tile, T = 3 where the ring of small problems eats
 // the gain of a fourth sweep (a batch of 32..256-wide grids).
 #define J3D_MSHAPES(M) \
-    M(8, 8, 4, 1)   \
-    M(8, 6, 4, 1)   \
-    M(8, 6, 5, 1)   \
-    M(8, 4, 4, 1)   \
-    M(8, 4, 3, 2)   \
-    M(8, 3, 4, 2)   \
-    M(8, 2, 4, 2)
+    M(8, 8, 4, 1, 1)   \
+    M(8, 6, 4, 1, 1)   \
+    M(8, 6, 5, 1, 1)   \
+    M(8, 4, 4, 1, 1)   \
+    M(8, 4, 3, 2, 1)   \
+    M(8, 3, 4, 2, 1)   \
+    M(8, 2, 4, 2, 1)
 
 struct MEntry {
-    int nw, ry, t, per_cu;
+    MShapeInfo info;
     void (*fn)(MultiArgs);
     void (*gen)(MultiArgs);
 };
-#define M(NW, RY, T, PC) {NW, RY, T, PC, multisweep_kernel<MShape<NW, RY, T>, false>, multisweep_kernel<MShape<NW, RY, T>, true>},
+#define M(NW, RY, T, PC, PG)                                                                                        \
+    {{NW * RY, T, NW * 64, {PC, PG}, {MShape<NW, RY, T>::lds(false), MShape<NW, RY, T>::lds(true)}},               \
+     multisweep_kernel<MShape<NW, RY, T>, false>, multisweep_kernel<MShape<NW, RY, T>, true>},
 const MEntry kM[] = {J3D_MSHAPES(M)};
 #undef M
 }  // namespace
 
 int mshape_count() { return (int)(sizeof kM / sizeof kM[0]); }
-MShapeInfo mshape_info(int i) { return MShapeInfo{kM[i].nw * kM[i].ry, kM[i].t, kM[i].nw * 64, kM[i].per_cu}; }
+MShapeInfo mshape_info(int i) { return kM[i].info; }
 
 int launch_multisweep(int shape, bool general, const MultiArgs &a, int grid, void *stream)
 {
@@ -613,7 +626,7 @@ int launch_multisweep(int shape, bool general, const MultiArgs &a, int grid, voi
         const int q = b.tile_count / kXcdCount, r = b.tile_count % kXcdCount;
         for (int x = 0; x <= kXcdCount; ++x) b.xcut[x] = x * q + (x < r ? x : r);
     }
-    hipLaunchKernelGGL((general ? kM[shape].gen : kM[shape].fn), dim3(grid), dim3(kM[shape].nw * 64), 0,
+    hipLaunchKernelGGL((general ? kM[shape].gen : kM[shape].fn), dim3(grid), dim3(kM[shape].info.threads), 0,
                        (hipStream_t)stream, b);
     return (int)hipGetLastError();
 }

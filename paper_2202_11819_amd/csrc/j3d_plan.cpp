@@ -295,9 +295,9 @@ int64_t multi_steps(const MShapeInfo &mi, int64_t planes)
 //   - the two overlap only in part: the third root of the sum of cubes.
 // Constants refitted to 5200 timings of 47 grids, with four other shapes,
 // measured 0.996 of the speed over 22 solves, batches and pools: not kept.
-double multi_cost(const MShapeInfo &mi, int cus, double tiles, double steps, double cells, bool ragged)
+double multi_cost(const MShapeInfo &mi, bool general, int cus, double tiles, double steps, double cells, bool ragged)
 {
-    const double c = std::min<double>(mi.per_cu, std::ceil(tiles / cus));  // workgroups sharing a compute unit
+    const double c = std::min<double>(mi.per_cu[general], std::ceil(tiles / cus));  // workgroups sharing a compute unit
     const int cpt = mi.rows * 64 / mi.threads;                             // cells per thread
     const double valu = mi.threads / 256 * (cpt * mi.t * 13.0 + 15) * 0.0018;
     const double step = c * valu + 0.3;
@@ -419,7 +419,7 @@ void make_multi(const Plan &plan, const std::vector<int32_t> *order, int cus, ui
                 cells += (double)pp.d.n[0] * pp.d.n[1] * pp.d.n[2];
                 const double sweeps = k + 1 < count ? (double)(pp.iters - prob(k + 1).iters)
                                                     : std::max<double>(1, (double)pp.iters);
-                if (sweeps > 0) cost += sweeps * multi_cost(mi, cus, tiles, steps / tiles, cells, ragged);
+                if (sweeps > 0) cost += sweeps * multi_cost(mi, m->general, cus, tiles, steps / tiles, cells, ragged);
             }
             if (!ok || tiles > (double)cap) break;
             if (best_shape < 0 || cost < best) {
