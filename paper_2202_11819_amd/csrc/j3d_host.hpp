@@ -49,6 +49,7 @@ struct ProbPlan {
     uint64_t field_cells = 0;     // doubles of one parity's fields (all blocks)
     uint64_t f_off[2] = {0, 0};   // bytes: start of the problem's fields per parity
     int64_t iters = 0;            // batch: sweeps to run
+    DenseShape dense;
 };
 
 struct Plan {
@@ -68,17 +69,8 @@ struct Plan {
 // (and at least the largest plane and face of every problem).
 j3d_status make_plan(int32_t count, const j3d_problem *probs, bool with_sr, Plan *plan);
 
-// What the dense copies of blocks [0, count) need to know.
-inline DenseShape dense_shape(const BlockDesc *blocks, size_t count)
-{
-    DenseShape d{1, 1, true};
-    for (size_t b = 0; b < count; ++b) {
-        d.max_plane = std::max(d.max_plane, blocks[b].ext[0] * blocks[b].ext[1]);
-        d.max_depth = std::max(d.max_depth, blocks[b].ext[2]);
-        d.even_rows = d.even_rows && blocks[b].ext[0] % 2 == 0;
-    }
-    return d;
-}
+// How the dense copies of a problem run: by blocks or by cells.
+DenseShape dense_shape(const Decomp &d);
 
 // Fills each block's fused-sweep halo sources and x-face targets (fx_*, fy_*,
 // fz_*) from its neighbour links and the neighbours' offsets; -1 where a face

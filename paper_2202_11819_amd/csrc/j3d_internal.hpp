@@ -243,13 +243,19 @@ int launch_exchange(double *base, const BlockDesc *blocks, int32_t block_begin, 
 int launch_unpack(double *base, const BlockDesc *blocks, int32_t block_begin, int32_t nblocks,
                   int32_t max_face, int parity, int face_mask, void *stream);
 // Dense global array chunk (planes z0..z1-1 of an n[0] x n[1] x ... grid) <->
-// block interiors of parity p.
+// block interiors of parity p.  maps: the problem's per-axis maps (x, y, z),
+// read unless d.by_block (one block needs none).
+constexpr int kDenseRun = 1024;  // cells of a workgroup's run, twice that in pairs
+constexpr bool dense_flat(int64_t max_plane, int per) { return max_plane < per / 2; }
 struct DenseShape {
     int32_t max_plane, max_depth;  // largest x-y plane (cells) and depth of the blocks
+    int32_t nb[3];                 // blocks per axis
     bool even_rows;                // every block is an even number of cells wide
+    bool by_block[2];              // by runs of blocks, cell by cell [0] or in pairs [1]; else by maps
 };
 int launch_dense(double *base, const BlockDesc *blocks, int32_t block_begin, int32_t nblocks, const DenseShape &d,
-                 const int64_t n[2], int64_t z0, int64_t z1, double *dense, int parity, bool to_dense, void *stream);
+                 const int32_t *maps, const int64_t n[3], int64_t z0, int64_t z1, double *dense, int parity,
+                 bool to_dense, void *stream);
 // Per-cell Dirichlet face f from a dense device array into both parities.
 int launch_set_face(double *base, const BlockDesc *blocks, int32_t block_base, const int32_t nb[3],
                     const int32_t *maps, const int64_t n[3], int face, const double *src,

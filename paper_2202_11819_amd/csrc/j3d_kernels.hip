@@ -866,14 +866,16 @@ struct DenseMap {
     int32_t nb0, nb1, nb2;
 };
 
-// Dense grid array <-> block interiors (planes z0 .. z1-1 of the grid).  A
-// workgroup copies runs of one block: rows are unpadded, so a block plane is
+// Dense grid array <-> block interiors (planes z0 .. z1-1 of the grid), in two
+// forms; dense_shape picks per problem by estimated time.
+//
+// By blocks: a workgroup copies runs of one block: rows are unpadded, so a block plane is
 // contiguous in the field, and only the dense side needs the cell's row, one
 // FP64 multiplication per cell ((e + 0.5) / d is at least 0.5 / d away from an
 // integer and e < 2^31, so the rounded product has the right floor).  Bound by
-// HBM; the earlier form found every cell from its dense index by three 64-bit
-// divisions and two table lookups.  512^3 as 8^3 blocks: out 726 -> 344 us, in
-// 685 -> 352 us (6.1 TB/s, the streaming copy's rate).
+// HBM: 512^3 as 8^3 blocks 344 us out, 352 us in (6.1 TB/s, the streaming
+// copy's rate), by cells 726 and 685 us.  Its grid is sized for the largest
+// block, and a run costs the same however few cells it has.
 // V: cells per access, 2 where every row starts on 16 bytes on both sides.
 // FLAT: runs over the whole block instead of one plane each, for blocks whose
 // planes would leave most of a workgroup idle (96^3 as 12^3 blocks: 8.7
@@ -883,7 +885,7 @@ __global__ __launch_bounds__(256) void dense_kernel(double *base, const BlockDes
                                                     int64_t n0, int64_t n1, int z0, int z1, double *dense, int parity)
 {
     typedef double vec __attribute__((ext_vector_type(V)));
-    constexpr int kRun = 4;  // accesses per thread in flight
+    constexpr int kRun = kDenseRun / 256;  // accesses per thread in flight
     for (int b = blockIdx.z; b < nblocks; b += gridDim.z) {
         const BlockDesc &B = blocks[block_begin + b];
         const int ex = B.ext[0], plane = ex * B.ext[1];
@@ -921,6 +923,32 @@ __global__ __launch_bounds__(256) void dense_kernel(double *base, const BlockDes
                         __builtin_nontemporal_store(v[u], reinterpret_cast<vec *>(to[u]));
             }
         }
+    }
+}
+
+// By cells: the dense array in its own order, each cell's place in its block by
+// three 64-bit divisions and the per-axis maps.  About 5.4 us per million
+// cells whatever the blocks: for small ones (512^3 as 64^3 blocks of 8^3: 0.79
+// against 1.87 ms by blocks), narrow ones, and extents that differ much (512^3
+// with 505 cells and seven single ones along each axis: 0.73 against 17 ms).
+template <bool OUT>
+__global__ __launch_bounds__(256) void dense_map_kernel(double *base, const BlockDesc *blocks, int block_base,
+                                                        DenseMap m, int64_t n0, int64_t n1, int64_t z0, int64_t count,
+                                                        double *dense, int parity)
+{
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < count; g += stride) {
+        const int64_t i = g % n0, j = (g / n0) % n1, k = z0 + g / (n0 * n1);
+        const int bx = m.mx[2 * i], lx = m.mx[2 * i + 1];
+        const int by = m.my[2 * j], ly = m.my[2 * j + 1];
+        const int bz = m.mz[2 * k], lz = m.mz[2 * k + 1];
+        const BlockDesc &B = blocks[block_base + bx + m.nb0 * (by + m.nb1 * bz)];
+        double *f = base + B.off[parity] + (int64_t)(lz + 1) * plane_stride(B.pitch, B.ext[1]) +
+                    (int64_t)(ly + 1) * B.pitch + lx;
+        if (OUT)
+            dense[g] = *f;
+        else
+            *f = dense[g];
     }
 }
 
@@ -1159,13 +1187,22 @@ int launch_shell(double *base, const BlockDesc *blocks, int32_t block_begin, int
 }
 
 int launch_dense(double *base, const BlockDesc *blocks, int32_t block_begin, int32_t nblocks, const DenseShape &d,
-                 const int64_t n[2], int64_t z0, int64_t z1, double *dense, int parity, bool to_dense, void *stream)
+                 const int32_t *maps, const int64_t n[3], int64_t z0, int64_t z1, double *dense, int parity,
+                 bool to_dense, void *stream)
 {
     const bool pairs = d.even_rows && n[0] % 2 == 0 && reinterpret_cast<uintptr_t>(dense) % 16 == 0;
-    const int per = 1024 * (pairs ? 2 : 1);  // cells of one workgroup's run
+    if (!d.by_block[pairs]) {
+        const DenseMap m{maps, maps + 2 * n[0], maps + 2 * (n[0] + n[1]), d.nb[0], d.nb[1], d.nb[2]};
+        const int64_t count = n[0] * n[1] * (z1 - z0);
+        hipLaunchKernelGGL((to_dense ? dense_map_kernel<true> : dense_map_kernel<false>),
+                           dim3(grid_for(count, 256, 65536)), dim3(256), 0, (hipStream_t)stream, base, blocks,
+                           block_begin, m, n[0], n[1], z0, count, dense, parity);
+        return (int)hipGetLastError();
+    }
+    const int per = kDenseRun * (pairs ? 2 : 1);
     const int64_t depth = d.max_depth < z1 - z0 ? d.max_depth : z1 - z0;
     // planes below half a run are copied block by block (block cells < 2^31)
-    const bool flat = d.max_plane < per / 2;
+    const bool flat = dense_flat(d.max_plane, per);
     const dim3 grid(grid_for(flat ? d.max_plane * depth : d.max_plane, per, 1 << 20),
                     flat ? 1 : (unsigned)(depth < kMaxGridY ? depth : kMaxGridY),
                     nblocks < kMaxGridY ? nblocks : kMaxGridY);

@@ -204,7 +204,7 @@ extern "C" j3d_status j3d_solve_noalloc(const j3d_problem *p, void *fields, uint
     unsigned long long *res = reinterpret_cast<unsigned long long *>(scr + lay.off_res);
     const int32_t nb = (int32_t)plan.blocks.size();
 
-    const DenseShape shape = dense_shape(plan.blocks.data(), plan.blocks.size());
+    const int32_t *dmaps = reinterpret_cast<const int32_t *>(scr + lay.off_maps);
     // ---- initial iterate: halo storage (Dirichlet values) and the interior ----
     int64_t maxc = 0, maxx = 0;
     for (const BlockDesc &B : plan.blocks) {
@@ -215,8 +215,8 @@ extern "C" j3d_status j3d_solve_noalloc(const j3d_problem *p, void *fields, uint
                                 interior_in ? 0 : 1, stream),
                     "init launch");
     if (st == J3D_OK && interior_in)
-        st = hip_status(launch_dense(base, dblocks, 0, nb, shape, n, 0, n[2], const_cast<double *>(interior_in), 0, false,
-                                     stream),
+        st = hip_status(launch_dense(base, dblocks, 0, nb, pp.dense, dmaps, n, 0, n[2],
+                                     const_cast<double *>(interior_in), 0, false, stream),
                         "scatter launch");
     if (st == J3D_OK && nb > 1 && !many) {
         hipLaunchKernelGGL(xhalo_pull_kernel, dim3((unsigned)std::min<int64_t>((maxx + 255) / 256, 1024),
@@ -268,7 +268,7 @@ extern "C" j3d_status j3d_solve_noalloc(const j3d_problem *p, void *fields, uint
         st = hip_status(launch_sweep(t.variant, a, a.tile_count, stream), "sweep launch");
     }
     if (st == J3D_OK)
-        st = hip_status(launch_dense(base, dblocks, 0, nb, shape, n, 0, n[2], interior_out, parity, true, stream),
+        st = hip_status(launch_dense(base, dblocks, 0, nb, pp.dense, dmaps, n, 0, n[2], interior_out, parity, true, stream),
                         "gather launch");
     if (st != J3D_OK) return st;
     if (!residual_out) return J3D_OK;

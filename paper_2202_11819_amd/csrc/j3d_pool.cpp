@@ -34,6 +34,7 @@ struct Req {
     uint32_t gen = 0;
     uint64_t region = 0, bytes = 0;
     BlockDesc blk;
+    DenseShape dense;
     int64_t n[3] = {0, 0, 0};
     int64_t iters_done = 0, max_iters = 0;
     double tol = 0.0, residual = 0.0;
@@ -184,7 +185,7 @@ j3d_status start_copy(j3d_pool *pl, int32_t slot)
     j3d_status st = hip_status(
         launch_dense(reinterpret_cast<double *>(pl->arena),
                      reinterpret_cast<const BlockDesc *>(pl->arena + pl->lay.off_blocks), slot, 1,
-                     dense_shape(&r.blk, 1), r.n, 0, r.n[2], dst, p, true, pl->stream),
+                     r.dense, nullptr, r.n, 0, r.n[2], dst, p, true, pl->stream),
         "result gather");
     if (st != J3D_OK) return st;
     st = hip_status(hipEventRecord(r.gather_ev, pl->stream), "gather event");
@@ -330,6 +331,7 @@ j3d_status j3d_pool_admit(j3d_pool *pl, const j3d_problem *p, int64_t max_iters,
         r.n[a] = d.n[a];
     }
     for (int f = 0; f < 6; ++f) r.blk.nbr[f] = -1;
+    r.dense = dense_shape(d);  // one block: by runs, no maps
     r.blk.pitch = (int32_t)row_pitch(d.n[0]);
     r.blk.prob = s;
     r.blk.face_total = 2 * (d.n[1] * d.n[2] + d.n[0] * d.n[2] + d.n[0] * d.n[1]);

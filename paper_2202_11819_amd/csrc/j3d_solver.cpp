@@ -151,10 +151,10 @@ j3d_status copy_dense(const Plan &plan, char *arena, int32_t i, int parity, doub
     const ProbPlan &pp = plan.probs[i];
     const int64_t *n = pp.d.n;
     const int64_t plane = n[0] * n[1];
-    const DenseShape shape = dense_shape(plan.blocks.data() + pp.block_begin, (size_t)pp.nblocks);
+    const int32_t *maps = reinterpret_cast<const int32_t *>(arena + pp.maps_off);
     auto copy = [&](int64_t z0, int64_t z1, double *at) {
-        return hip_status(launch_dense(dbase(arena), dblocks(plan, arena), pp.block_begin, pp.nblocks, shape, n, z0, z1,
-                                       at, parity, to_dense, stream),
+        return hip_status(launch_dense(dbase(arena), dblocks(plan, arena), pp.block_begin, pp.nblocks, pp.dense, maps, n,
+                                       z0, z1, at, parity, to_dense, stream),
                           to_dense ? "gather launch" : "scatter launch");
     };
     if (dense_on_device) return copy(0, n[2], dense);

@@ -20,6 +20,6 @@ def run_check(tmp_path, name):
     assert " 0 bad" in out.stdout
 
 
-@pytest.mark.parametrize("name", ["cut_axis_check", "mshape_check"])
+@pytest.mark.parametrize("name", ["cut_axis_check", "mshape_check", "dense_route_check"])
 def test_host_check(tmp_path, name):
     run_check(tmp_path, name)
