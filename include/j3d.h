@@ -77,9 +77,10 @@ typedef enum {
  *                 blocking, on decomposed grids too: a tile recomputes a ring
  *                 of its neighbours' cells instead of exchanging halos between
  *                 its iterations), captured into HIP graphs of an even number
- *                 of launches, replayed.  After j3d_set_tune with a shape, and
- *                 where the blocks lie too far apart or unequal ones are only a
- *                 few planes deep, it is FUSED | CAPTURED.
+ *                 of launches, replayed.  For a single iteration, after
+ *                 j3d_set_tune with a shape, and where the ring would outweigh
+ *                 the cells (grids of a few columns, blocks of a few planes) or
+ *                 the blocks lie too far apart, it is FUSED | CAPTURED.
  *  BLOCK_A/B/C:   the paper's fusion strategies at block granularity (one
  *                 launch stream of operations per block, like UNFUSED_BLOCK):
  *                 A fuses each block's six pack kernels into one; B also its
@@ -99,8 +100,9 @@ typedef enum {
  *                 (the one-cell shell that reads halos) is updated.  Every
  *                 cell is written once per iteration.
  *  TWO_SWEEP:     GRAPH's launches of several iterations each, not captured, on
- *                 a grid of one block, whatever shape j3d_set_tune chose.
- *                 EINVAL for a decomposed grid.  Not in the paper.
+ *                 a grid of one block, whatever shape j3d_set_tune chose; FUSED
+ *                 where they would be slower.  EINVAL for a decomposed grid.
+ *                 Not in the paper.
  *  CAPTURED:      a flag OR-ed with any mode: its iterations are captured once
  *                 into HIP graphs (50 sweeps per graph for FUSED, 24 launches
  *                 for TWO_SWEEP, 2 sweeps for the others, whose graphs hold
@@ -281,7 +283,7 @@ j3d_status j3d_batch_arena_bytes(int32_t count, const j3d_problem *probs, uint64
  * batch, as resolved by the caller's autotuner from its tune cache (the cache
  * itself, a file of measured shapes per device and problem mix, is kept by the
  * caller, not parsed here); NULL or {-1, 0, 0}: the library's choice, several
- * sweeps per launch.  EINVAL for count
+ * sweeps per launch where that is faster.  EINVAL for count
  * < 1, NULL arrays, a bad problem or a bad shape; ENOMEM if the arena is too
  * small; all before device work.                                            */
 j3d_status j3d_batch_create(int32_t count, const j3d_problem *probs, const int64_t *iters,

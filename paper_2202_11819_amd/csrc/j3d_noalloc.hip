@@ -167,11 +167,11 @@ extern "C" j3d_status j3d_solve_noalloc(const j3d_problem *p, void *fields, uint
     char *scr = nullptr;
     st = scratch_address(dev, &scr);
     if (st != J3D_OK) return st;
-    // several sweeps per launch if their tile table fits as well
+    // several sweeps per launch where that pays and their tile table fits as well
     MultiPlan multi;
-    make_multi(plan, nullptr, cus, kScratchBytes / sizeof(Tile), &multi);
+    if (iters > 1) make_multi(plan, nullptr, cus, kScratchBytes / sizeof(Tile), &multi, &t);
     const Layout mlay = scratch_layout(plan.blocks.size(), multi.tiles.size(), maps.size());
-    const bool many = multi.shape >= 0 && mlay.total <= kScratchBytes;
+    const bool many = multi.pays(iters) && mlay.total <= kScratchBytes;
     if (many) {
         tiles = std::move(multi.tiles);
         lay = mlay;

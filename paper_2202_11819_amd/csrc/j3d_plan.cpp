@@ -345,6 +345,47 @@ double multi_cost(const MShapeInfo &mi, bool general, int cus, double tiles, dou
     return (std::cbrt(compute * compute * compute + hbm * hbm * hbm) + 3.0) / mi.t;
 }
 
+// What a launch of the one-sweep kernel takes, from the blocks added so far.
+// Fitted to MI355X timings of 21 grids from 8^3 to 640^3, thin, uneven and
+// decomposed ones among them, within 20%: a compute unit takes a tile at a
+// time, 2.5 us and, for each plane it reads, 0.13 us and 0.31 us per 1024 cells
+// of the shape; memory moves the cells and the rings and planes around them at
+// 5.9 TB/s; third root of the sum of cubes.
+struct SingleCost {
+    VariantInfo vi;
+    int zchunk;  // 0: whole blocks
+    int64_t ex = 0, ey = 0, ez = 0;
+    double n = 0, steps = 0, moved = 0;  // of a block of these extents
+    double tiles = 0, all_steps = 0, cells = 0;
+
+    SingleCost(const j3d_tune &t) : vi(variant_info(t.variant)), zchunk(t.zchunk) {}
+
+    void add(const BlockDesc &B)
+    {
+        if (B.ext[0] != ex || B.ext[1] != ey || B.ext[2] != ez) {
+            ex = B.ext[0];
+            ey = B.ext[1];
+            ez = B.ext[2];
+            int64_t ntx, nty;
+            tiles_xy(vi, ex, ey, &ntx, &nty);
+            const int64_t ntz = zchunk > 0 ? ceil_div(ez, zchunk) : 1;
+            n = (double)(ntx * nty * ntz);
+            steps = (double)(ntx * nty) * (double)(ez + 2 * ntz);
+            moved = (double)(ex * ey) * (double)(2 * ez + 2 * ntz) + 2.0 * (double)(nty * ex + ntx * ey) * (double)ez;
+        }
+        tiles += n;
+        all_steps += steps;
+        cells += moved;
+    }
+    double us(int cus) const
+    {
+        if (tiles == 0) return 0;
+        const double step = 0.13 + 0.31 * (vi.tile_x ? vi.tile_x * vi.tile_y : vi.tile_y) / 1024;
+        const double compute = std::ceil(tiles / cus) * (all_steps / tiles * step + 2.5), hbm = cells * 8 / 5.9e6;
+        return std::cbrt(compute * compute * compute + hbm * hbm * hbm) + 0.5;
+    }
+};
+
 // Byte span of a tile's blocks from its first block's field: the lane offsets
 // are 32-bit.
 bool multi_span_ok(const Plan &plan, const ProbPlan &pp, const std::vector<Piece> &px, const std::vector<Piece> &py,
@@ -407,7 +448,8 @@ bool cut_z(const ProbPlan &pp, bool general, int t, int zc, F cut)
 
 }  // namespace
 
-void make_multi(const Plan &plan, const std::vector<int32_t> *order, int cus, uint64_t cap, MultiPlan *m)
+void make_multi(const Plan &plan, const std::vector<int32_t> *order, int cus, uint64_t cap, MultiPlan *m,
+                const j3d_tune *one)
 {
     m->shape = -1;
     m->general = false;
@@ -470,12 +512,22 @@ void make_multi(const Plan &plan, const std::vector<int32_t> *order, int cus, ui
     }
     if (best_shape < 0) return;
     const MShapeInfo mi = mshape_info(best_shape);
+    j3d_tune t1;
+    if (one)
+        t1 = *one;
+    else
+        default_tune(plan, cus, &t1);
+    SingleCost single(t1);
+    double steps = 0, cells = 0;
     for (int32_t k = 0; k < count; ++k) {
         const ProbPlan &pp = prob(k);
         cut_axis((int32_t)pp.d.n[0], 64, mi.t, x_align(pp), &px);
         cut_axis((int32_t)pp.d.n[1], mi.rows, mi.t, 1, &py);
         cut_z(pp, m->general, mi.t, best_zc, [&](int64_t at, int64_t len, int64_t n) {
-            for (int64_t i = 0; i < n; ++i)
+            for (int64_t i = 0; i < n; ++i) {
+                const int32_t z0 = (int32_t)(at + i * len / n), nzv = (int32_t)((i + 1) * len / n) - (int32_t)(i * len / n);
+                const int below = mi.t - std::min(mi.t, z0 + 1);  // no ramp below the boundary plane
+                steps += (double)(px.size() * py.size() * (multi_steps(mi, nzv) - below / 2 * 2));
                 for (const Piece &y : py)
                     for (const Piece &x : px) {
                         Tile t{};
@@ -484,12 +536,25 @@ void make_multi(const Plan &plan, const std::vector<int32_t> *order, int cus, ui
                         t.nxv = x.len;
                         t.y0 = y.at;
                         t.nyv = y.len;
-                        t.z0 = (int32_t)(at + i * len / n);
-                        t.nzv = (int32_t)((i + 1) * len / n - i * len / n);
+                        t.z0 = z0;
+                        t.nzv = nzv;
                         m->tiles.push_back(t);
                     }
+            }
         });
         m->prefix.push_back((int32_t)m->tiles.size());
+        cells += (double)pp.d.n[0] * pp.d.n[1] * pp.d.n[2];
+        for (int32_t b = pp.block_begin; b < pp.block_begin + pp.nblocks; ++b) single.add(plan.blocks[b]);
+        // what problem k has more than the next one, in launches and in sweeps
+        const int64_t more = k + 1 < count ? prob(k + 1).iters : 0;
+        const int64_t launches = ceil_div(pp.iters, mi.t) - ceil_div(more, mi.t);
+        const double tiles = (double)m->tiles.size();
+        if (k + 1 == count || pp.iters > more) {
+            m->launch_us = mi.t * multi_cost(mi, m->general, cus, tiles, steps / tiles, cells, ragged);
+            m->sweep_us = single.us(cus);
+            m->all_us += (double)launches * m->launch_us;
+            m->all_single_us += (double)(pp.iters - more) * m->sweep_us;
+        }
     }
     tile_work(m->tiles, &m->work);
     m->shape = best_shape;

@@ -436,19 +436,24 @@ j3d_status j3d_pool_step(j3d_pool *pl, int32_t sweeps)
         round.probs.push_back(std::move(pp));
     }
     if (round.probs.empty()) return J3D_OK;
+    auto share = [&](const Req &r, int64_t *limit) {  // sweeps of a request this round, and its next stop
+        *limit = r.max_iters;
+        if (r.check_every > 0) *limit = std::min(*limit, (r.iters_done / r.check_every + 1) * r.check_every);
+        return std::max<int64_t>(0, std::min<int64_t>(sweeps, *limit - r.iters_done));
+    };
+    int64_t longest = 0, limit = 0;
+    for (const BlockDesc &B : round.blocks) longest = std::max(longest, share(pl->reqs[B.prob], &limit));
     MultiPlan multi;
-    if (!pl->tuned || pl->two_sweep)
-        make_multi(round, nullptr, pl->cus, (uint64_t)pl->max_slots * kPoolTilesPerReq, &multi);
-    const bool many = multi.shape >= 0;
-    int64_t longest = 0;
+    if (longest > 1 && (!pl->tuned || pl->two_sweep)) {
+        const j3d_tune one{pl->variant, pl->zchunk, 0};
+        make_multi(round, nullptr, pl->cus, (uint64_t)pl->max_slots * kPoolTilesPerReq, &multi, &one);
+    }
+    const bool many = multi.pays(longest);
     for (const BlockDesc &B : round.blocks) {
         const int32_t s = B.prob;
         Req &r = pl->reqs[s];
         const int64_t base = r.iters_done;
-        int64_t limit = r.max_iters;
-        if (r.check_every > 0) limit = std::min(limit, (base / r.check_every + 1) * r.check_every);
-        const int64_t k = std::max<int64_t>(0, std::min<int64_t>(sweeps, limit - base));
-        longest = std::max(longest, k);
+        const int64_t k = share(r, &limit);
         ProbDesc &pd = pl->host_probs[s];
         std::memset(&pd, 0, sizeof pd);
         pd.res_slot = s;

@@ -691,7 +691,7 @@ j3d_status j3d_create(const j3d_problem *p, void *dev_arena, uint64_t arena_byte
     default_tune(s->plan, s->cus, &t);
     st = apply_tune(s, t, false);
     if (st == J3D_OK) {
-        make_multi(s->plan, nullptr, s->cus, s->plan.mtiles_cap, &s->multi);
+        make_multi(s->plan, nullptr, s->cus, s->plan.mtiles_cap, &s->multi, &t);
         st = upload_tables(s->plan, s->tiles, s->multi, s->arena, s->stream);
     }
     if (st == J3D_OK)
@@ -780,15 +780,15 @@ j3d_status j3d_run(j3d_solver *s, int64_t iters, j3d_mode mode_in, double *resid
     bool captured = (mode & J3D_CAPTURED) != 0;
     mode &= ~(int)J3D_CAPTURED;
     if (mode == J3D_GRAPH) {
-        // the same iterates by the fastest launches: several sweeps each,
-        // unless the caller chose the one-sweep kernel's shape
+        // the same iterates by the fastest launches: several sweeps each where
+        // that pays, unless the caller chose the one-sweep kernel's shape
         mode = J3D_FUSED;
         captured = true;
-        if (s->multi.shape >= 0 && !s->tuned) mode = J3D_TWO_SWEEP;
+        if (!s->tuned && s->multi.pays(iters)) mode = J3D_TWO_SWEEP;
     } else if (mode == J3D_TWO_SWEEP && s->plan.blocks.size() != 1) {
         return set_error(J3D_EINVAL, "the two-sweep mode needs a grid of one block (%zu blocks)",
                          s->plan.blocks.size());
-    } else if (mode == J3D_TWO_SWEEP && s->multi.shape < 0) {
+    } else if (mode == J3D_TWO_SWEEP && !s->multi.pays(iters)) {
         mode = J3D_FUSED;
     }
     if (mode < J3D_UNFUSED_BLOCK || mode > J3D_TWO_SWEEP)
@@ -958,7 +958,7 @@ j3d_status j3d_batch_create(int32_t count, const j3d_problem *probs, const int64
     std::stable_sort(b->order.begin(), b->order.end(),
                      [&](int32_t x, int32_t y) { return iters[x] > iters[y]; });
     b->tuned = tune && !(tune->variant == -1 && tune->zchunk == 0 && tune->blocks_per_cu == 0);
-    make_multi(b->plan, &b->order, cus, b->plan.mtiles_cap, &b->multi);
+    make_multi(b->plan, &b->order, cus, b->plan.mtiles_cap, &b->multi, &t);
     std::vector<Tile> tiles;
     b->prefix_tiles.assign(1, 0);
     for (int32_t k = 0; k < count; ++k) {
@@ -1076,7 +1076,7 @@ j3d_status j3d_batch_run(j3d_batch *b, double *residuals_out)
 {
     if (!b) return set_error(J3D_EINVAL, "batch is NULL");
     if (b->ran) return set_error(J3D_ESTATE, "batch already ran");
-    return batch_run(b, b->multi.shape >= 0 && !b->tuned, residuals_out);
+    return batch_run(b, !b->tuned && b->multi.pays_all(), residuals_out);
 }
 
 j3d_status j3d_batch_run_two_sweep(j3d_batch *b, double *residuals_out)
@@ -1087,7 +1087,7 @@ j3d_status j3d_batch_run_two_sweep(j3d_batch *b, double *residuals_out)
         if (b->plan.probs[i].nblocks != 1)
             return set_error(J3D_EINVAL, "two sweeps per launch need undivided problems (problem %zu has %d blocks)",
                              i, b->plan.probs[i].nblocks);
-    return batch_run(b, b->multi.shape >= 0, residuals_out);
+    return batch_run(b, b->multi.pays_all(), residuals_out);
 }
 
 j3d_status j3d_batch_get_interior(j3d_batch *b, int32_t i, double *dst, int dst_on_device)

@@ -20,6 +20,7 @@ def run_check(tmp_path, name):
     assert " 0 bad" in out.stdout
 
 
-@pytest.mark.parametrize("name", ["cut_axis_check", "mshape_check", "dense_route_check"])
+@pytest.mark.parametrize("name", ["cut_axis_check", "mshape_check", "dense_route_check",
+                                  "launch_choice_check"])
 def test_host_check(tmp_path, name):
     run_check(tmp_path, name)
