@@ -29,6 +29,12 @@ j3d_status upload_tiles(const Plan &plan, const std::vector<Tile> &tiles, char *
 // to run, the parity and the sweep count.
 MultiArgs multi_args(const Plan &plan, char *arena);
 
+// For the library's own checks, exported but no part of its interface: GRAPH and
+// TWO_SWEEP runs of this solver take launches of this shape from now on, for any
+// number of sweeps.  EINVAL for an unknown shape or one the grid's blocks do not
+// allow.
+extern "C" j3d_status j3d_check_multi_shape(j3d_solver *s, int32_t shape, int32_t *sweeps);
+
 // Seeded initialisation of every problem of a plan (interior of parity 0,
 // halo storage of both parities).
 j3d_status init_fields(const Plan &plan, char *arena, hipStream_t stream);

@@ -177,19 +177,23 @@ struct MultiPlan {
     std::vector<Tile> tiles;
     std::vector<uint64_t> work;
     std::vector<int32_t> prefix;  // tiles of the first k problems of `order`
-    // Estimated microseconds of a launch over all problems, here and by the
-    // one-sweep kernel, and of all their sweeps (ProbPlan::iters).
-    double launch_us = 0, sweep_us = 0, all_us = 0, all_single_us = 0;
+    // Estimated microseconds of a launch over all problems, of t sweeps, of up to
+    // kShortSweeps and by the one-sweep kernel; and of all their sweeps
+    // (ProbPlan::iters).
+    double launch_us = 0, short_us = 0, sweep_us = 0, all_us = 0, all_single_us = 0;
 
     // Whether every problem's next `sweeps` sweeps are faster several to a
-    // launch.  A launch costs about as much for fewer than t sweeps, so a
+    // launch.  A launch costs about as much for fewer sweeps than it has stages, so a
     // single sweep never is (512^3: 547 against 381 us, 64^3: 26 against 23);
     // thin grids that fill few of a tile's 64 lanes, and rows of blocks a few
     // planes deep, are not at any count (1 x 1024 x 1024, 50 sweeps: 2.29
     // against 1.12 ms).
+    bool always = false;  // shape named by a check: whatever the times
     bool pays(int64_t sweeps) const
     {
-        return shape >= 0 && sweeps > 1 && (double)((sweeps + t - 1) / t) * launch_us < (double)sweeps * sweep_us;
+        if (always) return shape >= 0;
+        const double rest = sweeps % t == 0 ? 0 : sweeps % t <= kShortSweeps ? short_us : launch_us;
+        return shape >= 0 && sweeps > 1 && (double)(sweeps / t) * launch_us + rest < (double)sweeps * sweep_us;
     }
     bool pays_all() const { return shape >= 0 && all_us < all_single_us; }
 };
@@ -209,9 +213,9 @@ int32_t cut_axis_count(int32_t n, int cap, int t, int align);
 // m->shape stays -1 where the one-sweep launches have to serve: a tile's blocks
 // lie further apart than a 32-bit offset reaches, or unequal blocks are
 // shallower than the sweeps of a launch.  one: the one-sweep shape to compare
-// with (NULL: the default).
+// with (NULL: the default).  only >= 0: by this shape or none.
 void make_multi(const Plan &plan, const std::vector<int32_t> *order, int cus, uint64_t cap, MultiPlan *m,
-                const j3d_tune *one = nullptr);
+                const j3d_tune *one = nullptr, int only = -1);
 
 // Problem descriptor of a plan's problem (sweeps 0 .. iters).
 void fill_prob(const Plan &plan, int32_t i, int64_t maps_base, ProbDesc *pd);

@@ -191,7 +191,9 @@ constexpr int flat_x0(int ex, int tnx, int tx)
 //   plain launch: nsweeps (1..T) sweeps from buffer `parity`;
 //   MS_MULTI: launch number `step` of a sequence.  A problem with `limit` sweeps
 //   takes part while step * T < limit, in buffer (base + step) & 1, and adds
-//   its residual with its last sweep (PF_RES_LAST).
+//   its residual with its last sweep (PF_RES_LAST).  nsweeps is the largest
+//   limit of the sequence.
+// With nsweeps <= kShortSweeps the two-stage form of the shape runs.
 enum : int32_t { MS_MULTI = 1, MS_RES = 2 };
 
 struct MultiArgs {
@@ -214,6 +216,7 @@ struct MultiArgs {
 struct MShapeInfo {
     int rows, t, threads, per_cu[2], lds[2];
 };
+constexpr int kShortSweeps = 2;
 constexpr int kMultiSegs = 3;  // block rows along z that a tile of unequal blocks may read
 int mshape_count();
 MShapeInfo mshape_info(int i);

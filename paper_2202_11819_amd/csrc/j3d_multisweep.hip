@@ -602,14 +602,17 @@ __global__ __launch_bounds__(S::NT)  void multisweep_kernel(MultiArgs a)
     M(8, 3, 4, 2, 1)   \
     M(8, 2, 4, 2, 1)
 
+// A launch of one or two sweeps runs the same tiles by the two-stage form of
+// its shape: fewer stages and a ramp of two planes instead of T.
 struct MEntry {
     MShapeInfo info;
-    void (*fn)(MultiArgs);
-    void (*gen)(MultiArgs);
+    void (*fn[2])(MultiArgs);   // T sweeps: equal, unequal blocks
+    void (*fn2[2])(MultiArgs);  // up to two
 };
 #define M(NW, RY, T, PC, PG)                                                                                        \
     {{NW * RY, T, NW * 64, {PC, PG}, {MShape<NW, RY, T>::lds(false), MShape<NW, RY, T>::lds(true)}},               \
-     multisweep_kernel<MShape<NW, RY, T>, false>, multisweep_kernel<MShape<NW, RY, T>, true>},
+     {multisweep_kernel<MShape<NW, RY, T>, false>, multisweep_kernel<MShape<NW, RY, T>, true>},                    \
+     {multisweep_kernel<MShape<NW, RY, 2>, false>, multisweep_kernel<MShape<NW, RY, 2>, true>}},
 const MEntry kM[] = {J3D_MSHAPES(M)};
 #undef M
 }  // namespace
@@ -626,7 +629,8 @@ int launch_multisweep(int shape, bool general, const MultiArgs &a, int grid, voi
         const int q = b.tile_count / kXcdCount, r = b.tile_count % kXcdCount;
         for (int x = 0; x <= kXcdCount; ++x) b.xcut[x] = x * q + (x < r ? x : r);
     }
-    hipLaunchKernelGGL((general ? kM[shape].gen : kM[shape].fn), dim3(grid), dim3(kM[shape].info.threads), 0,
+    const MEntry &e = kM[shape];
+    hipLaunchKernelGGL((a.nsweeps <= kShortSweeps ? e.fn2 : e.fn)[general], dim3(grid), dim3(e.info.threads), 0,
                        (hipStream_t)stream, b);
     return (int)hipGetLastError();
 }

@@ -499,6 +499,7 @@ j3d_status j3d_pool_step(j3d_pool *pl, int32_t sweeps)
         a.end = pl->arena + pl->arena_bytes;
         a.res = res;
         a.flags = MS_MULTI;
+        a.nsweeps = (int32_t)std::min<int64_t>(multi.t, longest);
         a.tile_count = (int32_t)tiles.size();
         const int grid = xcd_split(multi.work, 0, a.tile_count, a.xcut);
         for (int64_t j = 0; j * multi.t < longest && st == J3D_OK; ++j) {

@@ -765,6 +765,27 @@ j3d_status j3d_set_tune(j3d_solver *s, const j3d_tune *t)
     return st;
 }
 
+j3d_status j3d_check_multi_shape(j3d_solver *s, int32_t shape, int32_t *sweeps)
+{
+    if (!s || !sweeps) return set_error(J3D_EINVAL, "NULL argument");
+    if (shape < 0 || shape >= mshape_count()) return set_error(J3D_EINVAL, "no shape %d", shape);
+    MultiPlan m;
+    make_multi(s->plan, nullptr, s->cus, s->plan.mtiles_cap, &m, &s->tune, shape);
+    if (m.shape != shape) return set_error(J3D_EINVAL, "shape %d does not suit these blocks", shape);
+    j3d_status st = hip_status(hipMemcpyAsync(s->arena + s->plan.off_mtiles, m.tiles.data(),
+                                              m.tiles.size() * sizeof(Tile), hipMemcpyHostToDevice, s->stream),
+                               "tile upload");
+    const hipError_t w = hipStreamSynchronize(s->stream);
+    if (st == J3D_OK) st = hip_status(w, "tile upload");
+    if (st != J3D_OK) return st;
+    m.always = true;
+    s->multi = std::move(m);
+    s->tuned = false;
+    drop_graphs(s);
+    *sweeps = s->multi.t;
+    return J3D_OK;
+}
+
 j3d_status j3d_get_tune(const j3d_solver *s, j3d_tune *out)
 {
     if (!s || !out) return set_error(J3D_EINVAL, "NULL argument");
@@ -1031,6 +1052,7 @@ j3d_status batch_multi_sweep(j3d_batch *b)
     const int t = b->multi.t;
     MultiArgs a = multi_args(b->plan, b->arena);
     a.flags = MS_MULTI;
+    a.nsweeps = (int32_t)std::min<int64_t>(t, b->max_iters);
     int32_t active = count;
     for (int64_t k = 0; k * t < b->max_iters; ++k) {
         while (active > 0 && b->plan.probs[b->order[active - 1]].iters <= k * t) --active;
