@@ -328,7 +328,9 @@ int64_t multi_steps(const MShapeInfo &mi, int64_t planes)
 //   - a plane step issues about 13 instructions per cell, stage and wave
 //     (7 FP64, 4 DPP, 2 for the boundary) and 15 more, 1.8 ns each per SIMD,
 //     and waits about 0.3 us for LDS, barrier and dependent chains;
-//   - a tile starts with about 3 us of table lookups and first loads;
+//   - a tile starts with about 3 us of table lookups and first loads, with
+//     unequal blocks 0.9 us more for each of a thread's rows (256^3 in block
+//     rows of 5 planes: 200 us a launch by 64-row tiles, 158 without);
 //   - memory moves 17 bytes per cell and launch at 5.3 TB/s, at 3.2 TB/s where
 //     tiles end inside cache lines and the grid is past the last-level cache;
 //   - the two overlap only in part: the third root of the sum of cubes.
@@ -340,7 +342,8 @@ double multi_cost(const MShapeInfo &mi, bool general, int cus, double tiles, dou
     const int cpt = mi.rows * 64 / mi.threads;                             // cells per thread
     const double valu = mi.threads / 256 * (cpt * mi.t * 13.0 + 15) * 0.0018;
     const double step = c * valu + 0.3;
-    const double compute = std::ceil(tiles / (cus * c)) * (steps * step + 3.0);
+    const double start = general ? 3.0 + 0.9 * cpt : 3.0;
+    const double compute = std::ceil(tiles / (cus * c)) * (steps * step + start);
     const double hbm = cells * 17.0 / (ragged && cells > 1.6e7 ? 3.2e6 : 5.3e6);
     return (std::cbrt(compute * compute * compute + hbm * hbm * hbm) + 3.0) / mi.t;
 }

@@ -43,6 +43,24 @@ static void check(const char *name, const Ext &x, const Ext &y, const Ext &z, bo
         for (long k : {2, 3, 4, 8, 100}) expect(!m.pays(k), name, "thin grid", k);
 }
 
+// One count of a grid in block rows a few planes deep.
+static void check_rows(const char *name, const Ext &z, long k, bool pays)
+{
+    const Ext x{100, 156}, y{128, 128};
+    const Ext *ext[3] = {&x, &y, &z};
+    j3d_problem p{};
+    for (int a = 0; a < 3; ++a) {
+        p.nblk[a] = (int32_t)ext[a]->size();
+        p.split[a] = ext[a]->data();
+        for (int64_t e : *ext[a]) p.n[a] += e;
+    }
+    Plan plan;
+    expect(make_plan(1, &p, true, &plan) == J3D_OK, name, "plan", 0);
+    MultiPlan m;
+    make_multi(plan, nullptr, 256, plan.mtiles_cap, &m);
+    expect(m.pays(k) == pays, name, "sweeps", k);
+}
+
 static void check_batch(int64_t iters, bool pays)
 {
     j3d_problem p[3] = {};
@@ -77,6 +95,14 @@ int main()
     // measured 2 and 2.4 times as slow
     check("1 x 1024 x 1024", {1}, {1024}, {1024}, false);
     check("1 x 65536 x 1", {1}, {65536}, {1}, false);
+    // 341 against 306 us, 155 against 146; 2585 against 3420
+    Ext four = same(62, 4), five = same(50, 5);
+    four.push_back(3);
+    four.push_back(5);
+    five.push_back(6);
+    check_rows("256^3 in rows of 4 planes", four, 4, false);
+    check_rows("256^3 in rows of 5 planes", five, 2, false);
+    check_rows("256^3 in rows of 5 planes", five, 50, true);
     check_batch(0, false);
     check_batch(1, false);
     check_batch(100, true);
