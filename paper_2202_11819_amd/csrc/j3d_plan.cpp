@@ -236,11 +236,16 @@ uint64_t count_tiles(const Plan &plan, int variant, int zchunk)
 {
     const VariantInfo vi = variant_info(variant);
     const int zc = zchunk > 0 ? zchunk : max_ez(plan, 0, (int32_t)plan.blocks.size());
-    uint64_t n = 0;
+    uint64_t n = 0, of = 0;
+    const int32_t *last = nullptr;  // a block's neighbours in the table mostly have its extents
     for (const BlockDesc &B : plan.blocks) {
-        int64_t ntx, nty;
-        tiles_xy(vi, B.ext[0], B.ext[1], &ntx, &nty);
-        n += (uint64_t)(ntx * nty * ceil_div(B.ext[2], zc));
+        if (!last || B.ext[0] != last[0] || B.ext[1] != last[1] || B.ext[2] != last[2]) {
+            int64_t ntx, nty;
+            tiles_xy(vi, B.ext[0], B.ext[1], &ntx, &nty);
+            of = (uint64_t)(ntx * nty * ceil_div(B.ext[2], zc));
+            last = B.ext;
+        }
+        n += of;
     }
     return n;
 }
@@ -296,6 +301,7 @@ constexpr int kMinMultiZ = 4;
 
 int x_align(const ProbPlan &pp)
 {
+    if (pp.nblocks == 1) return pp.d.n[0] % 8 ? 1 : 8;
     for (int64_t e : pp.d.ext[0])
         if (e % 8) return 1;
     return 8;
@@ -336,15 +342,24 @@ int64_t multi_steps(const MShapeInfo &mi, int64_t planes)
 //   - the two overlap only in part: the third root of the sum of cubes.
 // Constants refitted to 5200 timings of 47 grids, with four other shapes,
 // measured 0.996 of the speed over 22 solves, batches and pools: not kept.
-double multi_cost(const MShapeInfo &mi, bool general, int cus, double tiles, double steps, double cells, bool ragged)
+// The planner asks for some 250 of them while a solver is created, so where the
+// larger part alone is above `worse` no root is taken (any value above it does).
+double multi_cost(const MShapeInfo &mi, bool general, int cus, double tiles, double steps, double cells, bool ragged,
+                  double worse = HUGE_VAL)
 {
-    const double c = std::min<double>(mi.per_cu[general], std::ceil(tiles / cus));  // workgroups sharing a compute unit
-    const int cpt = mi.rows * 64 / mi.threads;                             // cells per thread
+    auto up = [](double v) {
+        const double k = (double)(int64_t)v;
+        return k < v ? k + 1 : k;
+    };
+    const double c = std::min<double>(mi.per_cu[general], up(tiles / cus));  // workgroups sharing a compute unit
+    const int cpt = mi.rows * 64 / mi.threads;                              // cells per thread
     const double valu = mi.threads / 256 * (cpt * mi.t * 13.0 + 15) * 0.0018;
     const double step = c * valu + 0.3;
     const double start = general ? 3.0 + 0.9 * cpt : 3.0;
-    const double compute = std::ceil(tiles / (cus * c)) * (steps * step + start);
+    const double compute = up(tiles / (cus * c)) * (steps * step + start);
     const double hbm = cells * 17.0 / (ragged && cells > 1.6e7 ? 3.2e6 : 5.3e6);
+    const double least = (std::max(compute, hbm) + 3.0) / mi.t;
+    if (least > worse) return least;
     return (std::cbrt(compute * compute * compute + hbm * hbm * hbm) + 3.0) / mi.t;
 }
 
@@ -396,6 +411,9 @@ bool multi_span_ok(const Plan &plan, const ProbPlan &pp, const std::vector<Piece
 {
     const Decomp &d = pp.d;
     if (pp.nblocks == 1) return true;
+    const BlockDesc &first = plan.blocks[pp.block_begin], &last = plan.blocks[pp.block_begin + pp.nblocks - 1];
+    if ((last.off[0] - first.off[0] + block_field_cells(last.ext[0], last.ext[1], last.ext[2])) * 8 <= 0xFFFFF000ll)
+        return true;  // all of the problem's fields within reach
     auto owner = [](const std::vector<int64_t> &org, int64_t c) {
         return (int32_t)(std::upper_bound(org.begin(), org.end(), c) - org.begin()) - 1;
     };
@@ -454,9 +472,7 @@ bool cut_z(const ProbPlan &pp, bool general, int t, int zc, F cut)
 void make_multi(const Plan &plan, const std::vector<int32_t> *order, int cus, uint64_t cap, MultiPlan *m,
                 const j3d_tune *one, int only)
 {
-    m->shape = -1;
-    m->general = false;
-    m->tiles.clear();
+    *m = MultiPlan{};
     m->prefix.assign(1, 0);
     const int32_t count = (int32_t)(order ? order->size() : plan.probs.size());
     auto prob = [&](int32_t k) -> const ProbPlan & { return plan.probs[order ? (*order)[k] : k]; };
@@ -470,6 +486,34 @@ void make_multi(const Plan &plan, const std::vector<int32_t> *order, int cus, ui
         depth = std::max(depth, pp.d.n[2]);
         ragged = ragged || x_align(pp) == 1;
     }
+    // The z stretches to cut, those of equal depth together: a pool round of 256
+    // requests is planned while the GPU waits (250 us by requests, 60 by depths).
+    // The problems of a group run together for as many sweeps as they have more
+    // than the next group (a batch, longest first; else all in one).
+    struct Stretch {
+        int32_t group, len, k;
+    };
+    std::vector<Stretch> zs;
+    std::vector<double> group_sweeps, group_cells;
+    double cells = 0;
+    for (int32_t k = 0; k < count; ++k) {
+        const ProbPlan &pp = prob(k);
+        cut_z(pp, m->general, 0, 1, [&](int64_t, int64_t len, int64_t) {
+            zs.push_back({(int32_t)group_cells.size(), (int32_t)len, k});
+        });
+        cells += (double)pp.d.n[0] * pp.d.n[1] * pp.d.n[2];
+        if (k + 1 < count && pp.iters == prob(k + 1).iters) continue;
+        group_sweeps.push_back(k + 1 < count ? (double)(pp.iters - prob(k + 1).iters) : std::max(1.0, (double)pp.iters));
+        group_cells.push_back(cells);
+    }
+    std::sort(zs.begin(), zs.end(), [](const Stretch &a, const Stretch &b) {
+        return a.group != b.group ? a.group < b.group : a.len != b.len ? a.len < b.len : a.k < b.k;
+    });
+    struct Column {
+        int32_t group, len;
+        double xy;  // tiles of an x-y plane
+    };
+    std::vector<Column> columns;
     std::vector<Piece> px, py;
     std::vector<int64_t> xy(count);
     int best_shape = -1, best_zc = 0;
@@ -479,33 +523,39 @@ void make_multi(const Plan &plan, const std::vector<int32_t> *order, int cus, ui
         bool ok = only < 0 || s == only;
         for (int32_t k = 0; k < count && ok; ++k) {
             const ProbPlan &pp = prob(k);
-            cut_axis((int32_t)pp.d.n[0], 64, mi.t, x_align(pp), &px);
-            cut_axis((int32_t)pp.d.n[1], mi.rows, mi.t, 1, &py);
-            xy[k] = (int64_t)px.size() * (int64_t)py.size();
-            ok = multi_span_ok(plan, pp, px, py, mi.t);
+            xy[k] = (int64_t)cut_axis_count((int32_t)pp.d.n[0], 64, mi.t, x_align(pp)) *
+                    cut_axis_count((int32_t)pp.d.n[1], mi.rows, mi.t, 1);
+            if (pp.nblocks > 1) {
+                cut_axis((int32_t)pp.d.n[0], 64, mi.t, x_align(pp), &px);
+                cut_axis((int32_t)pp.d.n[1], mi.rows, mi.t, 1, &py);
+                ok = multi_span_ok(plan, pp, px, py, mi.t) && cut_z(pp, m->general, mi.t, 1, [](int64_t, int64_t, int64_t) {});
+            }
         }
-        int last_zc = 0;
-        for (int64_t nc = 1; ok && nc <= ceil_div(depth, kMinMultiZ); nc += 1 + (count > 1 ? nc / 8 : nc / 16)) {
-            const int zc = (int)ceil_div(depth, nc);
+        if (!ok) continue;
+        columns.clear();
+        for (const Stretch &z : zs)
+            if (!columns.empty() && columns.back().group == z.group && columns.back().len == z.len)
+                columns.back().xy += (double)xy[z.k];
+            else
+                columns.push_back({z.group, z.len, (double)xy[z.k]});
+        int32_t last_zc = 0;
+        for (int64_t nc = 1; nc <= ceil_div(depth, kMinMultiZ); nc += 1 + (count > 1 ? nc / 8 : nc / 16)) {
+            const int32_t zc = (int32_t)ceil_div(depth, nc);
             if (zc == last_zc) continue;
             last_zc = zc;
-            // the first k + 1 problems run together for as many sweeps as problem k
-            // has more than problem k + 1 (a batch, longest first; else all equal)
-            double tiles = 0, steps = 0, cells = 0, cost = 0;
-            for (int32_t k = 0; k < count && ok; ++k) {
-                const ProbPlan &pp = prob(k);
-                ok = cut_z(pp, m->general, mi.t, zc, [&](int64_t, int64_t len, int64_t n) {
-                    // n pieces: len % n of them a plane deeper than the others
-                    tiles += (double)(xy[k] * n);
-                    steps += (double)(xy[k] * (len % n * multi_steps(mi, len / n + 1) +
-                                               (n - len % n) * multi_steps(mi, len / n)));
-                });
-                cells += (double)pp.d.n[0] * pp.d.n[1] * pp.d.n[2];
-                const double sweeps = k + 1 < count ? (double)(pp.iters - prob(k + 1).iters)
-                                                    : std::max<double>(1, (double)pp.iters);
-                if (sweeps > 0) cost += sweeps * multi_cost(mi, m->general, cus, tiles, steps / tiles, cells, ragged);
+            double tiles = 0, steps = 0, cost = 0;
+            for (size_t i = 0; i < columns.size(); ++i) {
+                const Column &c = columns[i];
+                const int32_t n = (c.len - 1) / zc + 1, low = c.len / n, more = c.len - low * n;
+                // n pieces: `more` of them a plane deeper than the others
+                tiles += c.xy * n;
+                steps += c.xy * (double)(more * multi_steps(mi, low + 1) + (n - more) * multi_steps(mi, low));
+                if ((i + 1 == columns.size() || columns[i + 1].group != c.group) && group_sweeps[c.group] > 0)
+                    cost += group_sweeps[c.group] *
+                            multi_cost(mi, m->general, cus, tiles, steps / tiles, group_cells[c.group], ragged,
+                                       best_shape < 0 ? HUGE_VAL : best / group_sweeps[c.group]);
             }
-            if (!ok || tiles > (double)cap) break;
+            if (tiles > (double)cap) break;
             if (best_shape < 0 || cost < best) {
                 best = cost;
                 best_shape = s;
@@ -523,7 +573,8 @@ void make_multi(const Plan &plan, const std::vector<int32_t> *order, int cus, ui
     SingleCost single(t1);
     MShapeInfo mi2 = mi;
     mi2.t = kShortSweeps;
-    double steps = 0, steps2 = 0, cells = 0;
+    double steps = 0, steps2 = 0;
+    cells = 0;
     for (int32_t k = 0; k < count; ++k) {
         const ProbPlan &pp = prob(k);
         cut_axis((int32_t)pp.d.n[0], 64, mi.t, x_align(pp), &px);

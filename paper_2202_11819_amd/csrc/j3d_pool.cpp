@@ -420,15 +420,15 @@ j3d_status j3d_pool_step(j3d_pool *pl, int32_t sweeps)
     // than j * t sweeps to go; its descriptor counts this round's sweeps and
     // names the buffer that holds its current iterate.
     Plan round;  // the chosen requests as problems of one plan
+    round.blocks.reserve(cands.size());
+    round.probs.reserve(cands.size());
     for (int32_t s = 0; s < pl->max_slots; ++s) {
         Req &r = pl->reqs[s];
         if (r.state != R_RUNNING || !chosen[s]) continue;
-        ProbPlan pp;
+        ProbPlan pp;  // one block: its extents are the grid's
         for (int a = 0; a < 3; ++a) {
             pp.d.n[a] = r.n[a];
             pp.d.nb[a] = 1;
-            pp.d.ext[a].assign(1, r.n[a]);
-            pp.d.org[a].assign(1, 0);
         }
         pp.block_begin = (int32_t)round.blocks.size();
         pp.nblocks = 1;
@@ -467,11 +467,10 @@ j3d_status j3d_pool_step(j3d_pool *pl, int32_t sweeps)
         const int64_t flips = many ? (k + multi.t - 1) / multi.t : k;
         pl->round.push_back(RoundEntry{s, r.gen, base, limit, r.buf ^ (int)(flips & 1)});
         if (!many) {
-            Plan one;
-            one.blocks.assign(1, B);
-            const size_t at = tiles.size();
-            make_tiles(one, 0, 1, pl->variant, pl->zchunk, &tiles, nullptr);
-            for (size_t i = at; i < tiles.size(); ++i) tiles[i].block = s;
+            const int32_t at = (int32_t)(&B - round.blocks.data());
+            const size_t begin = tiles.size();
+            make_tiles(round, at, at + 1, pl->variant, pl->zchunk, &tiles, nullptr);
+            for (size_t i = begin; i < tiles.size(); ++i) tiles[i].block = s;
         }
     }
     if (many) {
