@@ -294,8 +294,9 @@ def batch_bytes_per_lup():
 def modes_side(spec):
     """ms per sweep of the overdecomposed grid in the unfused modes (per block
     and per phase), fused, fused captured in graphs, and graph (several sweeps
-    per launch); and whether the graph run equals the undivided grid's bit for
-    bit after the full sweep count."""
+    per launch); and whether the captured fused run, the timed one, equals the
+    undivided grid's run by several sweeps per launch bit for bit after the
+    full sweep count."""
     import torch
     from paper_2202_11819_amd import api
     n, sweeps = spec.n, spec.iters
@@ -315,7 +316,7 @@ def modes_side(spec):
             res["ms_per_sweep"][mode] = round(ms, 4)
             res.setdefault("GLUPs", {})[mode] = round(cells / ms / 1e6, 2)
     with api.Solver(n, nblk=spec.nblk, seed=spec.seed) as a, api.Solver(n, seed=spec.seed) as b:
-        a.run(sweeps, mode="graph")
+        a.run(sweeps, mode="fused+graph")
         b.run(sweeps, mode="graph")
         ua, ub = a.get_interior_device(), b.get_interior_device()
         res["graph_equals_undivided_bitwise"] = bool(torch.equal(ua.view(torch.int64), ub.view(torch.int64)))
