@@ -1,7 +1,7 @@
 // Host check of when several sweeps go into one launch (MultiPlan::pays and
 // pays_all, linked from libj3d.so): never for a single sweep, not where the
-// tiles' lanes or planes are mostly ring, always for long runs of ordinary
-// grids.  Exit status 0 when every case holds.
+// tiles' lanes or planes are mostly ring or blocks too far apart, always for
+// long runs of ordinary grids.  Exit status 0 when every case holds.
 #include <cstdio>
 #include <vector>
 
@@ -79,8 +79,27 @@ static void check_batch(int64_t iters, bool pays)
     expect(m.shape >= 0 && m.pays_all() == pays, "batch", "sweeps", iters);
 }
 
+// Blocks whose fields lie further apart than a 32-bit offset reaches.
+static void check_reach(int64_t nx, int32_t bx, int64_t edge, bool ok, const char *name)
+{
+    j3d_problem p{};
+    p.n[0] = nx;
+    p.n[1] = p.n[2] = edge;
+    p.nblk[0] = bx;
+    p.nblk[1] = p.nblk[2] = 1;
+    Plan plan;
+    expect(make_plan(1, &p, true, &plan) == J3D_OK, name, "plan", 0);
+    MultiPlan m;
+    make_multi(plan, nullptr, 256, plan.mtiles_cap, &m);
+    expect((m.shape >= 0) == ok, name, "shape", m.shape);
+    expect(ok || !m.pays(50), name, "fifty sweeps", 50);
+}
+
 int main()
 {
+    check_reach(1600, 2, 800, false, "two blocks of 800^3, 8.2 GB");
+    check_reach(1024, 2, 512, true, "two blocks of 512^3, 2.2 GB");
+    check_reach(1600, 1, 800, true, "one block of 8.2 GB");
     // measured 1.4 to 3 times as fast several to a launch (50 sweeps)
     check("33x35x31", {33}, {35}, {31}, true);
     check("64^3", {64}, {64}, {64}, true);
