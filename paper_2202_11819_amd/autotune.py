@@ -10,6 +10,7 @@ the mix, so a later batch of the same class reuses the choice.
 """
 from __future__ import annotations
 
+import functools
 import hashlib
 import json
 import math
@@ -37,6 +38,14 @@ def size_class(problems) -> str:
 
 def device_arch() -> str:
     return torch.cuda.get_device_properties(0).gcnArchName.split(":")[0]
+
+
+@functools.lru_cache(maxsize=None)
+def library_digest(path=j3d.LIB_PATH) -> str:
+    """Digest of the loaded library's file: neither its version nor its table of
+    one-sweep shapes changes with every kernel."""
+    with open(path, "rb") as f:
+        return hashlib.sha256(f.read()).hexdigest()[:12]
 
 
 def candidates(problems):
@@ -78,10 +87,9 @@ def tune_batch(problems, iters, sample_sweeps=24, cache_path=DEFAULT_CACHE, log=
     Two stages on a shortened copy of the mix: every suitable tile shape at
     z-chunk 32, then the `keep` best shapes over z-chunks and schedules.
     report=True returns (tune, candidates timed), 0 timed for a cache hit."""
-    # the key names the library build and its tile table, so a cache written
-    # by another build (whose variant indices may mean other shapes) is not used
-    table = hashlib.sha256(repr(j3d.variants()).encode()).hexdigest()[:12]
-    key = f"{device_arch()}|{j3d.j3d_version()}|{table}|batch|{size_class(problems)}"
+    # the key names the library build, so a cache written with another one (other
+    # kernels, other shapes behind a variant index) is not used
+    key = f"{device_arch()}|{j3d.j3d_version()}|{library_digest()}|batch|{size_class(problems)}"
     cache = {}
     if cache_path and os.path.exists(cache_path):
         with open(cache_path) as f:
