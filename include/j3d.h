@@ -237,8 +237,12 @@ j3d_status j3d_set_interior(j3d_solver *s, const double *src, int src_on_device)
  * boundary lets linear fields be checked as exact fixed points.             */
 j3d_status j3d_set_face(j3d_solver *s, int32_t face, const double *src, int src_on_device);
 
-/* Choose the sweep kernel shape (see j3d_tune); NULL restores the default.
- * EINVAL for a variant out of range or a negative field.  Not in the paper. */
+/* Choose the one-sweep kernel's shape (see j3d_tune); NULL restores the
+ * default.  A shape or chunk named here is kept by GRAPH too, which then takes
+ * one sweep per launch (TWO_SWEEP does not); with {-1, 0, 0}, which names
+ * neither, GRAPH chooses by itself as after NULL.  Writing back what
+ * j3d_get_tune gave names a shape.  EINVAL for a variant out of range or a
+ * negative field.  Not in the paper.                                         */
 j3d_status j3d_set_tune(j3d_solver *s, const j3d_tune *t);
 
 /* The shape in use (the default chosen by block size until j3d_set_tune).
@@ -360,18 +364,18 @@ j3d_status j3d_pool_set_policy(j3d_pool *pl, int64_t fill_cells, int32_t max_wai
                                int32_t backlog_share);
 
 /* One-sweep kernel shape of the pool's rounds, which advance one sweep per
- * launch then: variant (-1 keeps the default
- * flattened 512-thread tile) and zchunk (>= 1 planes per tile, default 32);
- * blocks_per_cu must be 0.
- * NULL restores the default, several sweeps per launch.  ESTATE unless every
- * slot is free (a request's
- * tile count is checked against the pool's tile table at admission).       */
+ * launch then: variant (-1 keeps the default flattened 512-thread tile) and
+ * zchunk (>= 1 planes per tile, default 32, always named: 0 is EINVAL);
+ * blocks_per_cu must be 0.  NULL restores the default: several sweeps per launch
+ * where that is faster.  ESTATE unless every slot is free (a request's tile count
+ * is checked against the pool's tile table at admission).                    */
 j3d_status j3d_pool_set_tune(j3d_pool *pl, const j3d_tune *t);
 
-/* enable 1: rounds advance requests several sweeps per launch even after
- * j3d_pool_set_tune.  Results, residuals and check points are unchanged
- * (bit-identical).  enable 0: as j3d_pool_set_tune says (the default).  Only while the pool is empty (ESTATE
- * otherwise); EINVAL for other values.  Not in the paper.                  */
+/* enable 1: rounds advance requests several sweeps per launch, where that is
+ * faster, even after j3d_pool_set_tune.  Results, residuals and check points are
+ * unchanged (bit-identical).  enable 0: as j3d_pool_set_tune says (the default).
+ * Only while the pool is empty (ESTATE otherwise); EINVAL for other values.  Not
+ * in the paper.                                                              */
 j3d_status j3d_pool_set_two_sweep(j3d_pool *pl, int32_t enable);
 
 /* Non-blocking progress: retires a completed round (updating every request's

@@ -37,7 +37,9 @@ class Solver:
         return C.j3d_run(self.h, iters, mode, residual)
 
     def set_tune(self, variant=-1, zchunk=0, blocks_per_cu=0):
-        C.j3d_set_tune(self.h, variant, zchunk, blocks_per_cu)
+        """Shape of the one-sweep kernel, kept by mode "graph" too (one sweep per
+        launch then); None restores the library's choice."""
+        C.j3d_set_tune(self.h, -1 if variant is None else variant, zchunk, blocks_per_cu, default=variant is None)
 
     def get_tune(self):
         """(variant, zchunk, blocks_per_cu) in use."""
@@ -185,8 +187,9 @@ class Pool:
         C.j3d_pool_set_policy(self.h, fill_cells, max_wait_rounds, backlog_share)
 
     def set_tune(self, variant=-1, zchunk=32):
-        """Tile shape of the rounds; only while no request is admitted."""
-        C.j3d_pool_set_tune(self.h, variant, zchunk)
+        """Tile shape of the rounds, one sweep per launch then; None restores the
+        library's choice.  Only while no request is admitted."""
+        C.j3d_pool_set_tune(self.h, -1 if variant is None else variant, zchunk, default=variant is None)
 
     def set_two_sweep(self, enable=True):
         """Several sweeps per launch in the rounds, also after set_tune; only while no

@@ -31,8 +31,9 @@ MultiArgs multi_args(const Plan &plan, char *arena);
 
 // For the library's own checks, exported but no part of its interface: GRAPH and
 // TWO_SWEEP runs of this solver take launches of this shape from now on, for any
-// number of sweeps.  EINVAL for an unknown shape or one the grid's blocks do not
-// allow.
+// number of sweeps; sweeps receives its sweeps per launch.  EINVAL for an unknown
+// shape or one the grid's blocks do not allow.  Shape -1 changes nothing: sweeps
+// receives those per launch of a GRAPH run of 50.
 extern "C" j3d_status j3d_check_multi_shape(j3d_solver *s, int32_t shape, int32_t *sweeps);
 
 // Seeded initialisation of every problem of a plan (interior of parity 0,

@@ -761,13 +761,18 @@ j3d_status j3d_set_tune(j3d_solver *s, const j3d_tune *t)
         default_tune(s->plan, s->cus, &d);
     }
     const j3d_status st = apply_tune(s, d);
-    if (st == J3D_OK) s->tuned = t != nullptr;
+    // variant -1 without a chunk or schedule names no shape, as for a batch
+    if (st == J3D_OK) s->tuned = t && !(t->variant == -1 && t->zchunk == 0 && t->blocks_per_cu == 0);
     return st;
 }
 
 j3d_status j3d_check_multi_shape(j3d_solver *s, int32_t shape, int32_t *sweeps)
 {
     if (!s || !sweeps) return set_error(J3D_EINVAL, "NULL argument");
+    if (shape == -1) {
+        *sweeps = !s->tuned && s->multi.pays(50) ? s->multi.t : 1;
+        return J3D_OK;
+    }
     if (shape < 0 || shape >= mshape_count()) return set_error(J3D_EINVAL, "no shape %d", shape);
     MultiPlan m;
     make_multi(s->plan, nullptr, s->cus, s->plan.mtiles_cap, &m, &s->tune, shape);

@@ -66,6 +66,35 @@ def test_batches_of_few_sweeps(env, most, two, tune):
             assert np.array_equal(batch.get_interior(i), want) and res[i] == want_r, i
 
 
+def test_tune_names_a_shape_or_not(env):
+    # GRAPH keeps to a shape the program named, and to nothing else
+    import ctypes
+    _, api, j3d = env
+    look = j3d._lib.j3d_check_multi_shape
+    look.argtypes = [ctypes.c_void_p, ctypes.c_int32, ctypes.POINTER(ctypes.c_int32)]
+
+    def sweeps(s):
+        v = ctypes.c_int32()
+        assert look(s.h, -1, ctypes.byref(v)) == j3d.J3D_OK
+        return v.value
+
+    with api.Solver((64, 64, 64)) as s:
+        several = sweeps(s)
+        assert several > 1
+        default = s.get_tune()
+        for tune, want in (((25, 16, 0), 1), ((-1, 0, 0), several), ((-1, 32, 0), 1), ((None,), several),
+                           (default, 1), ((), several)):
+            s.set_tune(*tune)
+            assert sweeps(s) == want, tune
+        s.set_tune(None)
+        assert s.get_tune() == default
+    with api.Pool(1 << 24, max_slots=1) as pool:
+        pool.set_tune(25, 16)
+        pool.set_tune(None)
+        with pytest.raises(j3d.J3DError):
+            pool.set_tune(-1, 0)
+
+
 def test_single_sweeps_between_several(env):
     # a single sweep reads halos that a launch of several leaves stale
     oracle, api, _ = env
