@@ -239,4 +239,37 @@ inline uint64_t align_up(uint64_t v, uint64_t a) { return (v + a - 1) / a * a; }
 
 constexpr int kMinZchunk = 4;
 
+// ---- tables of the one-shot solve -------------------------------------------------
+
+constexpr uint64_t kScratchBytes = 4ull << 20;  // block, problem, tile and map tables, residual word
+
+struct ScratchLayout {
+    uint64_t off_blocks, off_probs, off_tiles, off_maps, off_res, total;
+};
+
+inline ScratchLayout scratch_layout(size_t nblocks, size_t ntiles, size_t nmaps)
+{
+    ScratchLayout l;
+    uint64_t o = 0;
+    l.off_blocks = o;
+    o = align_up(o + nblocks * sizeof(BlockDesc), 256);
+    l.off_probs = o;
+    o = align_up(o + sizeof(ProbDesc), 256);
+    l.off_tiles = o;
+    o = align_up(o + ntiles * sizeof(Tile), 256);
+    l.off_maps = o;
+    o = align_up(o + nmaps * sizeof(int32_t), 256);
+    l.off_res = o;
+    o = align_up(o + sizeof(uint64_t), 256);
+    l.total = o;
+    return l;
+}
+
+// Tiles that fit beside these blocks and maps.
+inline uint64_t scratch_tiles(size_t nblocks, size_t nmaps)
+{
+    const uint64_t rest = scratch_layout(nblocks, 0, nmaps).total;
+    return rest < kScratchBytes ? (kScratchBytes - rest) / sizeof(Tile) : 0;
+}
+
 }  // namespace j3d

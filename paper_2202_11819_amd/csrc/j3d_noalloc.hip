@@ -1,10 +1,11 @@
 // j3d_noalloc.hip -- a solve that allocates no device memory.
 //
-// j3d_solve_noalloc runs the launches of j3d_run (several sweeps each; where
-// their tables do not fit the scratch, the fused sweep, one launch per
-// iteration for all blocks) on fields that live in memory the caller passes, and keeps everything else it needs on the device (block and
-// problem descriptors, the tile table, the per-axis maps of the dense
-// copies, the residual word) in one file-scope device array of fixed size.
+// j3d_solve_noalloc runs the launches of j3d_run's GRAPH mode (several sweeps
+// each where that pays, else the fused sweep, one launch per iteration for all
+// blocks) on fields that live in memory the caller passes, and keeps everything
+// else it needs on the device (block and problem descriptors, the tile table,
+// the per-axis maps of the several-sweeps launches and of the copies by cells,
+// the residual word) in one file-scope device array of fixed size.
 // It is for callers that cannot allocate: code under stream capture, tight
 // serving loops, harnesses that forbid allocation.  It calls no hipMalloc,
 // hipFree, hipHostMalloc, graph or stream creation.
@@ -24,8 +25,6 @@
 #include "j3d_device.hpp"
 
 namespace j3d {
-
-constexpr uint64_t kScratchBytes = 4ull << 20;  // descriptor, tile and map tables
 
 // The scratch array.  In host code this name is only a stand-in for the
 // symbol: its device address comes from hipGetSymbolAddress (per device), and
@@ -78,28 +77,6 @@ __global__ __launch_bounds__(256) void xhalo_pull_kernel(double *base, const Blo
             }
         }
     }
-}
-
-struct Layout {
-    uint64_t off_blocks, off_probs, off_tiles, off_maps, off_res, total;
-};
-
-Layout scratch_layout(size_t nblocks, size_t ntiles, size_t nmaps)
-{
-    Layout l;
-    uint64_t o = 0;
-    l.off_blocks = o;
-    o = align_up(o + nblocks * sizeof(BlockDesc), 256);
-    l.off_probs = o;
-    o = align_up(o + sizeof(ProbDesc), 256);
-    l.off_tiles = o;
-    o = align_up(o + ntiles * sizeof(Tile), 256);
-    l.off_maps = o;
-    o = align_up(o + nmaps * sizeof(int32_t), 256);
-    l.off_res = o;
-    o = align_up(o + sizeof(uint64_t), 256);
-    l.total = o;
-    return l;
 }
 
 }  // namespace
@@ -159,7 +136,7 @@ extern "C" j3d_status j3d_solve_noalloc(const j3d_problem *p, void *fields, uint
                 maps.push_back(b);
                 maps.push_back((int32_t)l);
             }
-    Layout lay = scratch_layout(plan.blocks.size(), tiles.size(), maps.size());
+    ScratchLayout lay = scratch_layout(plan.blocks.size(), tiles.size(), maps.size());
     if (lay.total > kScratchBytes)
         return set_error(J3D_EINVAL, "problem needs %llu bytes of tables (%zu blocks, %zu tiles), more than the %llu "
                          "of the static scratch", (unsigned long long)lay.total, plan.blocks.size(), tiles.size(),
@@ -167,14 +144,13 @@ extern "C" j3d_status j3d_solve_noalloc(const j3d_problem *p, void *fields, uint
     char *scr = nullptr;
     st = scratch_address(dev, &scr);
     if (st != J3D_OK) return st;
-    // several sweeps per launch where that pays and their tile table fits as well
+    // several sweeps per launch where that pays, by tiles that fit beside the rest
     MultiPlan multi;
-    if (iters > 1) make_multi(plan, nullptr, cus, kScratchBytes / sizeof(Tile), &multi, &t);
-    const Layout mlay = scratch_layout(plan.blocks.size(), multi.tiles.size(), maps.size());
-    const bool many = multi.pays(iters) && mlay.total <= kScratchBytes;
+    if (iters > 1) make_multi(plan, nullptr, cus, scratch_tiles(plan.blocks.size(), maps.size()), &multi, &t);
+    const bool many = multi.pays(iters);
     if (many) {
         tiles = std::move(multi.tiles);
-        lay = mlay;
+        lay = scratch_layout(plan.blocks.size(), tiles.size(), maps.size());
     }
 
     // ---- tables into the scratch (the host copies are consumed before return) ----

@@ -21,6 +21,6 @@ def run_check(tmp_path, name):
 
 
 @pytest.mark.parametrize("name", ["cut_axis_check", "mshape_check", "dense_route_check",
-                                  "launch_choice_check"])
+                                  "launch_choice_check", "scratch_check"])
 def test_host_check(tmp_path, name):
     run_check(tmp_path, name)
