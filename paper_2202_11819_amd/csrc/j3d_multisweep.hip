@@ -154,8 +154,8 @@ struct MGeo {
 // Streams one tile.  GEN: blocks of unequal extents (plane strides differ from
 // lane to lane).  EDGE: some column or row of the tile's lanes lies on the
 // boundary layer; XE: a column does, so its values come from the x-halo
-// arrays.  RES: the launch's last sweep is measured; returns its maximum.
-template <class S, bool GEN, bool EDGE, bool XE, bool RES>
+// arrays.  Returns the last sweep's largest change where it is asked for.
+template <class S, bool GEN, bool EDGE, bool XE>
 __device__ __forceinline__ double multi_tile(const MGeo &g, double *E, double *LX, uint32_t *tab, int64_t *xtab)
 {
     constexpr int NW = S::NW, RY = S::RY, T = S::T;
@@ -442,7 +442,7 @@ __device__ __forceinline__ double multi_tile(const MGeo &g, double *E, double *L
 #pragma unroll
                 for (int r = 0; r < RY; ++r) keep_here(v[r]);
             }
-            if (RES && s == T - 1 && q >= g.z0 && q < g.z0 + g.nzv) {
+            if (s == T - 1 && g.res && q >= g.z0 && q < g.z0 + g.nzv) {
 #pragma unroll
                 for (int r = 0; r < RY; ++r) {
                     const double d = (vlane | srow(r)) == 0u ? fabs(v[r] - St[s][j ^ 1][r]) : 0.0;
@@ -559,14 +559,12 @@ __global__ __launch_bounds__(S::NT)  void multisweep_kernel(MultiArgs a)
     double rmax = 0.0;
     // every stage computes cells strictly inside the grid along x and y
     const bool xe = g.x0 < T || g.x0 + g.nxv + T > g.nx, ye = g.y0 < T || g.y0 + g.nyv + T > g.ny;
-    if (g.res)
-        rmax = multi_tile<S, GEN, true, true, true>(g, E, LX, tab, xtab);
-    else if (xe)
-        multi_tile<S, GEN, true, true, false>(g, E, LX, tab, xtab);
+    if (xe)
+        rmax = multi_tile<S, GEN, true, true>(g, E, LX, tab, xtab);
     else if (ye)
-        multi_tile<S, GEN, true, false, false>(g, E, LX, tab, xtab);
+        rmax = multi_tile<S, GEN, true, false>(g, E, LX, tab, xtab);
     else
-        multi_tile<S, GEN, false, false, false>(g, E, LX, tab, xtab);
+        rmax = multi_tile<S, GEN, false, false>(g, E, LX, tab, xtab);
     if (g.res) {
         double m = rmax;
 #pragma unroll
