@@ -1,11 +1,12 @@
 """Tile-shape / schedule search for the batched form.
 
-The batched form advances many independent problems with one launch per
-sweep; the kernel shape (tile variant, z-chunk) and the schedule (one
+The batched form advances many independent problems by one launch for all of
+them.  Chosen here, by timing short batched runs of the actual problem mix on
+the device: the library's own launches (several sweeps each), or one sweep per
+launch with a kernel shape (tile variant, z-chunk) and a schedule (one
 workgroup per tile, or a persistent grid of blocks_per_cu workgroups per
-compute unit taking tiles from per-XCD queues) are chosen here by timing
-short batched runs of the actual problem mix on the device.  Results are
-cached in a JSON file keyed by the device architecture and a size class of
+compute unit taking tiles from per-XCD queues).  Results are cached in a JSON
+file keyed by the device architecture, the library build and a size class of
 the mix, so a later batch of the same class reuses the choice.
 """
 from __future__ import annotations

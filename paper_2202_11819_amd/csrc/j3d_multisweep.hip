@@ -15,29 +15,31 @@
 //     strip's two ends, from the neighbouring waves through LDS; the plane
 //     above arrives from the stage before.  So the LDS carries 2 rows in RY
 //     instead of every cell, and one barrier per plane serves all T stages.
-//   - What bounds it: vector issue.  Seven FP64 operations and four DPP moves
-//     per update and lane, times the ring's share of lanes (64 x 64 lanes hold
-//     56 x 56 cells at T = 4), come to 0.29 ms per 4 sweeps of 512^3 at one
-//     instruction in 4 cycles; with barriers and ramps 0.38 ms without any
-//     memory access, 0.51 ms with it, 0.56 ms with the boundary tiles.
+//   - What bounds it: vector issue and memory, overlapping in part.  Seven FP64
+//     operations and four DPP moves per update and lane, times the ring's share
+//     of lanes (64 x 64 lanes hold 56 x 56 cells at T = 4), are 168 k vector
+//     instructions per SIMD for 4 sweeps of 512^3: 0.34 ms at the 2.0 ns that an
+//     FP64 or DPP instruction was measured to take.  The launch moves 2.42 GB,
+//     0.39 ms at the streaming copy's 6.15 TB/s, and takes 0.54 ms.
 //   - Measured and rejected: the x neighbours through the LDS crossbar
 //     (ds_bpermute for one side: 16.2 against 14.2 ms per 100 sweeps of 512^3,
 //     for both 21), two more planes of prefetch (the same), non-temporal
 //     loads (10% slower: the ring cells of a tile are its neighbours' cells
 //     and are found in L2).
 //
-// 512^3 as 8^3 blocks of 64^3: 138 us a sweep (970 GLUP/s) against 386 us one
-// sweep per launch; 64^3: 4.0 against 11.6 us; 33x35x31: 4.0 against 11.4 us
-// (a sweep's share of a whole checked pass).
+// 512^3 as 8^3 blocks of 64^3: 134 us a sweep (1000 GLUP/s) against 384 us one
+// sweep per launch; 64^3: 3.6 against 11.4 us; 33x35x31: 3.3 against 11.4 us
+// (a sweep's share of 50, with the call).
 //
 // Each value is the 7-term sum of the same operands in the same order as in a
 // single sweep (centre, x-, x+, y-, y+, z-, z+, each addition rounded, then
 // one multiplication by fl(1/7); built with -ffp-contract=off), so the result
 // has the bits of separate sweeps.  Cells of the Dirichlet layer keep their
 // value through the stages; what lies beyond it is never an operand of a
-// stored cell.  A launch of fewer than T sweeps lets its first stages pass
-// their input on.  Halos between blocks are read as the neighbours' interior
-// cells, so nothing is packed, exchanged or handed over.
+// stored cell.  A launch of fewer sweeps than it has stages lets the first ones
+// pass their input on; one or two sweeps run in a form of two stages.  Halos
+// between blocks are read as the neighbours' interior cells, so nothing is
+// packed, exchanged or handed over.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>

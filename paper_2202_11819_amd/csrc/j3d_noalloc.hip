@@ -244,7 +244,8 @@ extern "C" j3d_status j3d_solve_noalloc(const j3d_problem *p, void *fields, uint
         st = hip_status(launch_sweep(t.variant, a, a.tile_count, stream), "sweep launch");
     }
     if (st == J3D_OK)
-        st = hip_status(launch_dense(base, dblocks, 0, nb, pp.dense, dmaps, n, 0, n[2], interior_out, parity, true, stream),
+        st = hip_status(launch_dense(base, dblocks, 0, nb, pp.dense, dmaps, n, 0, n[2], interior_out, parity, true,
+                                     stream),
                         "gather launch");
     if (st != J3D_OK) return st;
     if (!residual_out) return J3D_OK;

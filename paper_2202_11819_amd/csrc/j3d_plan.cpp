@@ -330,10 +330,11 @@ int64_t multi_steps(const MShapeInfo &mi, int64_t planes)
 
 // Estimated microseconds per sweep of a launch of `tiles` tiles of `steps`
 // plane steps each.  Fitted to MI355X timings of every shape on 13 grids from
-// 33x35x31 to 1024^3 (within 15% of the fastest shape's time on each):
+// 33x35x31 to 1024^3:
 //   - a plane step issues about 13 instructions per cell, stage and wave
-//     (7 FP64, 4 DPP, 2 for the boundary) and 15 more, 1.8 ns each per SIMD,
-//     and waits about 0.3 us for LDS, barrier and dependent chains;
+//     (7 FP64, 4 DPP, 2 for the boundary) and 15 more, and waits about 0.3 us
+//     for LDS, barrier and dependent chains; the fit gives an instruction 1.8
+//     ns per SIMD, where FP64 and DPP ones alone measured 2.0;
 //   - a tile starts with about 3 us of table lookups and first loads, with
 //     unequal blocks 0.9 us more for each of a thread's rows (256^3 in block
 //     rows of 5 planes: 200 us a launch by 64-row tiles, 158 without);
@@ -503,7 +504,8 @@ void make_multi(const Plan &plan, const std::vector<int32_t> *order, int cus, ui
         });
         cells += (double)pp.d.n[0] * pp.d.n[1] * pp.d.n[2];
         if (k + 1 < count && pp.iters == prob(k + 1).iters) continue;
-        group_sweeps.push_back(k + 1 < count ? (double)(pp.iters - prob(k + 1).iters) : std::max(1.0, (double)pp.iters));
+        group_sweeps.push_back(k + 1 < count ? (double)(pp.iters - prob(k + 1).iters)
+                                             : std::max(1.0, (double)pp.iters));
         group_cells.push_back(cells);
     }
     std::sort(zs.begin(), zs.end(), [](const Stretch &a, const Stretch &b) {
@@ -528,7 +530,8 @@ void make_multi(const Plan &plan, const std::vector<int32_t> *order, int cus, ui
             if (pp.nblocks > 1) {
                 cut_axis((int32_t)pp.d.n[0], 64, mi.t, x_align(pp), &px);
                 cut_axis((int32_t)pp.d.n[1], mi.rows, mi.t, 1, &py);
-                ok = multi_span_ok(plan, pp, px, py, mi.t) && cut_z(pp, m->general, mi.t, 1, [](int64_t, int64_t, int64_t) {});
+                ok = multi_span_ok(plan, pp, px, py, mi.t) &&
+                     cut_z(pp, m->general, mi.t, 1, [](int64_t, int64_t, int64_t) {});
             }
         }
         if (!ok) continue;
@@ -581,7 +584,7 @@ void make_multi(const Plan &plan, const std::vector<int32_t> *order, int cus, ui
         cut_axis((int32_t)pp.d.n[1], mi.rows, mi.t, 1, &py);
         cut_z(pp, m->general, mi.t, best_zc, [&](int64_t at, int64_t len, int64_t n) {
             for (int64_t i = 0; i < n; ++i) {
-                const int32_t z0 = (int32_t)(at + i * len / n), nzv = (int32_t)((i + 1) * len / n) - (int32_t)(i * len / n);
+                const int32_t z0 = (int32_t)(at + i * len / n), nzv = (int32_t)(at + (i + 1) * len / n) - z0;
                 const int below = mi.t - std::min(mi.t, z0 + 1);  // no ramp below the boundary plane
                 steps += (double)(px.size() * py.size() * (multi_steps(mi, nzv) - below / 2 * 2));
                 steps2 += (double)(px.size() * py.size() * multi_steps(mi2, nzv));

@@ -2,8 +2,8 @@
 //
 // Requests are admitted while others run, as long as a slot and enough of the
 // HBM budget are free; their grids stay resident in the arena.  A round is a
-// few fused sweeps (one launch per sweep) over the tiles of every running
-// request; each request advances at its own pace and parity.  A residual is
+// number of sweeps over the tiles of the requests it holds, several per launch
+// where that is faster; each request advances at its own pace and parity.  A residual is
 // evaluated at every check point (every check_every sweeps and at the last);
 // a round never carries a request past its next check point, so the early
 // exit (residual <= tol) is decided at exactly that sweep.  Finished requests
@@ -22,8 +22,8 @@ using namespace j3d;
 
 namespace {
 
-// 64x32 tiles of 256 threads and 32-plane z-chunks: enough workgroups per
-// request that a round of a few mid-sized requests fills the GPU
+// one-sweep tiles of 32-plane z-chunks: enough workgroups per request that a
+// round of a few mid-sized requests fills the GPU
 constexpr int kPoolZchunk = 32;
 constexpr int64_t kPoolTilesPerReq = 4096;
 
@@ -297,7 +297,9 @@ j3d_status j3d_pool_admit(j3d_pool *pl, const j3d_problem *p, int64_t max_iters,
     int64_t ntx, nty;
     tiles_xy(vi, d.n[0], d.n[1], &ntx, &nty);
     const int64_t tiles = ntx * nty * ((d.n[2] + pl->zchunk - 1) / pl->zchunk);
-    // with several sweeps per launch asked for, 64 x 16 columns of 64 planes bound the request as well
+    // No launch uses columns of 64 x 16 cells and 64 planes.  They were the tiles of
+    // a former kernel, which set_two_sweep chose and whose table they had to fit;
+    // the bound stays, so that a pool refuses the requests it always has.
     const int64_t tiles2 = pl->two_sweep ? ((d.n[0] + 63) / 64) * ((d.n[1] + 15) / 16) * ((d.n[2] + 63) / 64) : 0;
     if (tiles > kPoolTilesPerReq || tiles2 > kPoolTilesPerReq)
         return set_error(J3D_EINVAL, "request of %lldx%lldx%lld needs %lld tiles, more than %lld",

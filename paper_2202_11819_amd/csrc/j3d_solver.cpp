@@ -153,8 +153,8 @@ j3d_status copy_dense(const Plan &plan, char *arena, int32_t i, int parity, doub
     const int64_t plane = n[0] * n[1];
     const int32_t *maps = reinterpret_cast<const int32_t *>(arena + pp.maps_off);
     auto copy = [&](int64_t z0, int64_t z1, double *at) {
-        return hip_status(launch_dense(dbase(arena), dblocks(plan, arena), pp.block_begin, pp.nblocks, pp.dense, maps, n,
-                                       z0, z1, at, parity, to_dense, stream),
+        return hip_status(launch_dense(dbase(arena), dblocks(plan, arena), pp.block_begin, pp.nblocks, pp.dense, maps,
+                                       n, z0, z1, at, parity, to_dense, stream),
                           to_dense ? "gather launch" : "scatter launch");
     };
     if (dense_on_device) return copy(0, n[2], dense);
@@ -297,8 +297,8 @@ j3d_status sweep_tiles(j3d_solver *s, int parity, bool fused, bool res, int32_t 
     return hip_status(launch_sweep(s->tune.variant, a, cnt, st), "sweep launch");
 }
 
-// Launches per HIP graph (one_sweep calls; a TWO_SWEEP launch performs two
-// sweeps): an even number, so a replay returns to the same buffer parity.  A
+// Launches per HIP graph (one_sweep calls; a TWO_SWEEP launch performs
+// multi.t sweeps): an even number, so a replay returns to the same buffer parity.  A
 // fused sweep is one node; the per-block modes put thousands of nodes into
 // one sweep, so their graphs hold two.
 int graph_sweeps(int mode) { return mode == J3D_FUSED ? 50 : mode == J3D_TWO_SWEEP ? 24 : 2; }
