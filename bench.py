@@ -270,7 +270,9 @@ def side_configs(args, spec):
     b = serve.batch_bench(log=log)
     out["batched"] = {k: b[k] for k in ("value", "unit", "batched_s", "tune", "tile", "autotune",
                                        "per_problem_loop_s", "per_problem_loop_GLUPs", "speedup_vs_loop", "config")}
-    out["batched"]["hbm_frac"] = round(b["value"] * batch_bytes_per_lup() / HBM_PEAK_GBPS, 4)
+    # the bytes of an update are those of one sweep per launch
+    out["batched"]["hbm_frac"] = (round(b["value"] * batch_bytes_per_lup() / HBM_PEAK_GBPS, 4)
+                                  if b["tune"][0] >= 0 else None)
     log("[bench] config: served form")
     sv = serve.serve_bench(count=args.requests, load=args.load, log=log)
     out["served"] = {k: sv[k] for k in ("value", "unit", "pool", "serial_plain", "p99_vs_serial", "mix_vs_alone",
@@ -279,8 +281,8 @@ def side_configs(args, spec):
 
 
 def batch_bytes_per_lup():
-    """Algorithmic bytes per cell update of the batched workload (interior read
-    and write plus the Dirichlet halo reads, weighted by sweeps)."""
+    """Algorithmic bytes per cell update of the batched workload, one sweep per
+    launch (interior read and write plus the Dirichlet halo reads, weighted by sweeps)."""
     from paper_2202_11819_amd import workloads as W
     lups = byts = 0
     for s in W.batch():
